@@ -133,7 +133,8 @@ int wc_set_option(wc_ctx* ctx, int option, int value);
 
 /* Right-hand sides handled together, per storage precision prec: nr_dirac per lane of D
  * (1..4), nr_sap per work-group of the plain block solver and nr_sap_eo of the even/odd one
- * (1..2; FP64 1).  0 leaves the library's choice (or the autotuner's).  Errors: WC_ERR_ARG. */
+ * (1..2; FP64 1).  0 leaves the library's choice (or the autotuner's).  wc_apply_D in FP64 runs
+ * one rhs per lane whatever the tile (the solvers' FP64 D follows it).  Errors: WC_ERR_ARG. */
 int wc_set_tiles(wc_ctx* ctx, int prec, int nr_dirac, int nr_sap, int nr_sap_eo);
 
 /* Create a context for one lattice: copies the gauge field U (device, complex128, see
@@ -156,7 +157,8 @@ int wc_clover_export(wc_ctx* ctx, void* A, void* stream);
 /* out = D in (region WC_FULL) or the block-diagonal sum of the Dirichlet block operators
  * D_Lambda in (WC_BLOCKS: hops between different blocks dropped, Sec. 4).  dagger = 1
  * applies D^dag = g5 D g5.  prec selects storage/arithmetic; inputs and outputs are
- * complex128 in any case (converted on the device).  in and out must not overlap. */
+ * complex128 in any case (converted on the device; in FP64 the kernel works on them directly
+ * and nothing is allocated).  in and out must not overlap. */
 int wc_apply_D(wc_ctx* ctx, void* out, const void* in, int nrhs, int prec, int region, int dagger, void* stream);
 
 /* One Schwarz half-sweep (Sec. 4): nmr MR steps from a zero start on every block of the
@@ -238,7 +240,8 @@ int wc_spinor_scale(wc_ctx* ctx, void* out, const void* in, int nrhs, double coe
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Arguments,
  * layouts and results are those of wc_apply_D (same kernels, bit-identical output).  The
  * packed input and output fields and the kernels' work list live in a fixed scratch array
- * of 128 MiB per GPU that the library holds until the process ends; a call needs
+ * of 128 MiB per GPU that the library holds until the process ends (FP64 does not touch it,
+ * under the same limit); a call needs
  * 256 B + 16 B per 256-site chunk and rhs tile + 2 x nrhs x V x (192 B FP64, 96 B FP32,
  * 52 B 16-bit), e.g. 16^3 x 32 in FP64 up to 2 right-hand sides.  Larger requests return
  * WC_ERR_ARG.  The operator must already be resident in prec (the FP64 one always is; any

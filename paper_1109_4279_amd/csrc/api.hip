@@ -1492,6 +1492,21 @@ int wc_clover_export(wc_ctx* c, void* A, void* stream) {
   });
 }
 
+// FP64 D_w straight between the caller's arrays (no packed fields, nothing allocated)
+static void apply_D_canon(wc_ctx* c, void* out, const void* in, int nrhs, int region, int dagger, hipStream_t st) {
+  DiracCanonLaunch a;
+  a.g = c->g;
+  a.gauge = c->links[P_F64].p;
+  a.clov = c->clov[P_F64].p;
+  a.in = (const double2*)in;
+  a.out = (double2*)out;
+  a.nrhs = nrhs;
+  a.dagger = dagger ? 1 : 0;
+  a.block = region == WC_BLOCKS;
+  launch_dirac_canon(a, st);
+  HIPCK(hipGetLastError());
+}
+
 int wc_apply_D(wc_ctx* c, void* out, const void* in, int nrhs, int prec, int region, int dagger, void* stream) {
   return guarded([&] {
     require(c && out && in && nrhs >= 1, WC_ERR_ARG, "null argument or nrhs < 1");
@@ -1499,6 +1514,10 @@ int wc_apply_D(wc_ctx* c, void* out, const void* in, int nrhs, int prec, int reg
     require(region == WC_FULL || region == WC_BLOCKS, WC_ERR_ARG, "bad region");
     require(c->have_clover, WC_ERR_STATE, "clover term not created");
     hipStream_t st = S(stream);
+    if (prec == WC_F64) {
+      apply_D_canon(c, out, in, nrhs, region, dagger, st);
+      return;
+    }
     Batch& B = ctx_batch(c, nrhs);
     B.ain[prec].ensure(prec, B.sites_rhs);
     B.aout[prec].ensure(prec, B.sites_rhs);
@@ -1557,8 +1576,12 @@ int wc_apply_D_noalloc(wc_ctx* c, void* out, const void* in, int nrhs, int prec,
     require(need <= SCRATCH_BYTES, WC_ERR_ARG,
             "wc_apply_D_noalloc: " + std::to_string(need >> 20) + " MiB of scratch needed for this lattice, nrhs " +
                 "and precision; the limit is " + std::to_string(SCRATCH_BYTES >> 20) + " MiB");
-    char* base = (char*)scratch_setup(c->dev);
     hipStream_t st = S(stream);
+    if (prec == WC_F64) {
+      apply_D_canon(c, out, in, nrhs, region, dagger, st);
+      return;
+    }
+    char* base = (char*)scratch_setup(c->dev);
     LatDesc L;
     std::memset(&L, 0, sizeof L);
     L.g = g;

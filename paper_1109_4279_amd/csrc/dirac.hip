@@ -257,4 +257,179 @@ void launch_dirac(int prec, int nr, const DiracLaunch& a, int grid, hipStream_t 
   }
 }
 
+// D_w in FP64 from and to the canonical arrays of the C interface (complex128
+// [rhs][lexicographic site][4][3]) in one launch, without a packed copy of the input or of
+// the output.  Bound by memory: spinor in and out, links and clover, the neighbours out of
+// the chunk and, for several right-hand sides, the operator from the caches.  Against
+// pack + k_dirac + unpack: 16^3 x 32 one rhs 78.6 -> 48.6 us a call (40.5 us in the kernel;
+// its 201 MB at the rate of a device copy take 41.5), 24^3 x 48 with 12 rhs 3.06 -> 1.74 ms,
+// 32^3 x 64 one rhs 0.74 ms (0.66 at the copy rate).
+//
+// A work-group takes one chunk of WG consecutive sites of the tile-major order and one
+// right-hand side, one lane per site; the work-groups of a chunk's right-hand sides are
+// neighbours on one XCD, whose L2 serves them the operator.  (Groups of two and three rhs
+// sharing a work-group of 512 and 768 lanes were slower: 24^3 x 48 with 12 rhs 1.76 / 2.05 /
+// 2.16 ms, 16^3 x 32 with two rhs 56 / 65 us.)  The chunk's spinors are staged in LDS: a
+// canonical site is 192 contiguous bytes, so the copy runs over (site, component) with the
+// component fastest (runs of B3 sites are contiguous) and the lanes then read component rows;
+// rows are one element longer than the chunk, which spreads the copy's 12 rows over the LDS
+// banks.  Hops inside the chunk read LDS, the others gather 192 contiguous bytes from the
+// canonical array.  The result goes back through the same LDS rows, with non-temporal stores
+// (the output then does not displace the input: 12 rhs 1.76 -> 1.74 ms, 32^3 x 64 0.77 -> 0.74).
+constexpr int DC_ROW = WG + 1;
+
+// Loads of this kernel: a uniform base (pointer and row, kept in scalar registers) plus one
+// 32-bit byte offset per site, so that the rows of a link or clover block share one address
+// register (16 bytes x V < 4 GiB: a lattice of 2^28 sites would not fit the GPU's memory).
+WC_D gd2v ld_row(const void* base, size_t row, unsigned off) {
+  return *(gptr_t<gd2v>)((const __attribute__((address_space(1))) char*)base + row * 16 + off);
+}
+WC_D SU3<double> canon_link(const void* gauge, int V, int mu, unsigned off) {
+  SU3<double> u;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    const gd2v v = ld_row(gauge, (size_t)(mu * 9 + k) * V, off);
+    u.m[k / 3][k % 3] = {v.x, v.y};
+  }
+  return u;
+}
+WC_D Herm6<double> canon_clover(const void* clov, int V, int blk, unsigned off) {
+  Herm6<double> h;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const gd2v v = ld_row(clov, (size_t)(18 * blk + k) * V, off);
+    h.d[2 * k] = v.x;
+    h.d[2 * k + 1] = v.y;
+  }
+#pragma unroll
+  for (int k = 0; k < 15; ++k) {
+    const gd2v v = ld_row(clov, (size_t)(18 * blk + 3 + k) * V, off);
+    h.o[k] = {v.x, v.y};
+  }
+  return h;
+}
+
+__global__ __launch_bounds__(WG) void k_dirac_canon(DiracCanonLaunch a) {
+  typedef double R;
+  extern __shared__ double stage_d[];
+  double2* st = (double2*)stage_d;       // [12][DC_ROW]
+  int* lexs = (int*)(st + 12 * DC_ROW);  // [WG] canonical site indices
+  const Geom& g = a.g;
+  const int it = xcd_remap(blockIdx.x, gridDim.x);
+  const int chunk = it / a.nrhs, r = it - chunk * a.nrhs;
+  const int t = threadIdx.x;
+  const int s0 = chunk * WG;
+  const bool valid = s0 + t < g.V;
+  const int s = valid ? s0 + t : g.V - 1;
+  const int tile = s / g.bvol;
+  int tc[4], lc[4], x[4];
+  tile_coords(g, tile, tc);
+  local_coords(g, s - tile * g.bvol, lc);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) x[m] = tc[m] * g.B[m] + lc[m];
+  const int lex = ((x[0] * g.L[1] + x[1]) * g.L[2] + x[2]) * g.L[3] + x[3];
+  lexs[t] = lex;
+  const double2* in = a.in + (size_t)r * g.V * 12;
+  __syncthreads();
+  const int nel = (s0 + WG <= g.V ? WG : g.V - s0) * 12;
+#pragma unroll
+  for (int j = 0; j < 12; ++j) {
+    const int e = j * WG + t;
+    if (e < nel) {
+      const int site = e / 12, k = e - site * 12;
+      st[k * DC_ROW + site] = gld_d2(in, (size_t)lexs[site] * 12 + k);
+    }
+  }
+  __syncthreads();
+
+  // input spinor at the site with internal index n and canonical index nlex
+  auto input = [&](int n, int nlex) {
+    Spinor<R> p;
+    const unsigned ln = (unsigned)(n - s0);
+    if (ln < (unsigned)WG) {
+#pragma unroll
+      for (int k = 0; k < 12; ++k) {
+        const double2 v = st[k * DC_ROW + ln];
+        p.c[k / 3][k % 3] = {v.x, v.y};
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 12; ++k) {
+        const double2 v = gld_d2(in, (size_t)nlex * 12 + k);
+        p.c[k / 3][k % 3] = {v.x, v.y};
+      }
+    }
+    if (a.dagger) g5(p);
+    return p;
+  };
+
+  Spinor<R> acc;
+  zero(acc);
+  if (valid) {
+    auto hop = [&](auto MUc) {
+      constexpr int MU = decltype(MUc)::value;
+      const int stride = MU == 3 ? 1 : MU == 2 ? g.L[3] : MU == 1 ? g.L[3] * g.L[2] : g.L[3] * g.L[2] * g.L[1];
+      const int wrap = (g.L[MU] - 1) * stride;
+      int ph;
+      bool same;
+      const int nf = neighbour(g, s, tile, tc, lc, MU, +1, &ph, &same);
+      if (!a.block || same) {
+        const SU3<R> u = canon_link(a.gauge, g.V, MU, 16u * s);
+        const Spinor<R> p = input(nf, x[MU] + 1 < g.L[MU] ? lex + stride : lex - wrap);
+        accum_recon<R, MU, -1>(acc, mul_U(u, project<R, MU, -1>(p)), R(ph));
+      }
+      const int nb = neighbour(g, s, tile, tc, lc, MU, -1, &ph, &same);
+      if (!a.block || same) {
+        const SU3<R> u = canon_link(a.gauge, g.V, MU, 16u * nb);
+        const Spinor<R> p = input(nb, x[MU] > 0 ? lex - stride : lex + wrap);
+        accum_recon<R, MU, +1>(acc, mul_Udag(u, project<R, MU, +1>(p)), R(ph));
+      }
+    };
+    hop(std::integral_constant<int, 0>());
+    hop(std::integral_constant<int, 1>());
+    hop(std::integral_constant<int, 2>());
+    hop(std::integral_constant<int, 3>());
+
+    // clover and the -1/2 of the hopping term; acc becomes the result
+    const Spinor<R> self = input(s, lex);
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+      const Herm6<R> hc = canon_clover(a.clov, g.V, blk, 16u * s);
+      cplx<R> v[6], o[6];
+#pragma unroll
+      for (int i = 0; i < 6; ++i) v[i] = self.c[2 * blk + i / 3][i % 3];
+      herm6_apply(hc, v, o);
+#pragma unroll
+      for (int i = 0; i < 6; ++i) {
+        cplx<R>& q = acc.c[2 * blk + i / 3][i % 3];
+        q = o[i] - R(0.5) * q;
+      }
+    }
+    if (a.dagger) g5(acc);
+  }
+  __syncthreads();  // every lane has read the staged input
+  if (valid) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k)
+      st[k * DC_ROW + t] = make_double2(acc.c[k / 3][k % 3].re, acc.c[k / 3][k % 3].im);
+  }
+  __syncthreads();
+  double2* out = a.out + (size_t)r * g.V * 12;
+#pragma unroll
+  for (int j = 0; j < 12; ++j) {
+    const int e = j * WG + t;
+    if (e < nel) {
+      const int site = e / 12, k = e - site * 12;
+      const double2 v = st[k * DC_ROW + site];
+      __builtin_nontemporal_store(gd2v{v.x, v.y}, (gd2v*)(out + (size_t)lexs[site] * 12 + k));
+    }
+  }
+}
+
+void launch_dirac_canon(const DiracCanonLaunch& a, hipStream_t st) {
+  const int nchunks = (a.g.V + WG - 1) / WG;
+  const size_t lds = sizeof(double2) * 12 * DC_ROW + sizeof(int) * WG;
+  hipLaunchKernelGGL(k_dirac_canon, dim3((unsigned)nchunks * a.nrhs), dim3(WG), lds, st, a);
+}
+
 }  // namespace wc

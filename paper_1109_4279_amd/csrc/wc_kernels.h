@@ -38,6 +38,20 @@ WC_D bool cycle_dead(const int* dead) { return dead && gld_i32(dead, 0) != 0; }
 size_t dirac_stage_lds_bytes(int prec, int nr);  // dynamic LDS of a staged D_w launch
 constexpr size_t LDS_MAX_BYTES = 160 * 1024;       // LDS a gfx950 work-group may allocate
 
+// D_w in FP64 on the canonical arrays of one lattice (complex128 [nrhs][V][4][3]); links and
+// clover in the library's FP64 storage
+struct DiracCanonLaunch {
+  Geom g;
+  const void* gauge;
+  const void* clov;
+  const double2* in;
+  double2* out;
+  int nrhs;
+  int dagger;  // apply gamma5 D gamma5
+  int block;   // Dirichlet-block operator instead of the full one
+};
+void launch_dirac_canon(const DiracCanonLaunch& a, hipStream_t st);
+
 // ----------------------------------------------------------------- Schwarz block MR
 struct SapLaunch {
   const LatDesc* lats;
