@@ -271,7 +271,8 @@ int wc_force(wc_ctx* ctx, void* F, const void* phi, const wc_solver_params* p, w
  * RHS tile of D in prec, of the outer solver's FP64 D (and, for 16-bit prec, its FP32 D of
  * an F32 basis) and of both block solvers in prec, and keep the fastest in the context.
  * nr_out[0..3] receive the chosen tiles: D in prec, FP64 D, plain block solver, even/odd
- * block solver. */
+ * block solver (1 also where the library's own choice, which may be the kernel that takes
+ * several rhs on the matrix cores, was the fastest; the context then keeps that choice). */
 int wc_autotune(wc_ctx* ctx, int nrhs, int prec, int nr_out[4], void* stream);
 
 /* Choose the Schwarz block shape of the context among the valid shapes with at most 256

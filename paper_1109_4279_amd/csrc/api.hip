@@ -213,9 +213,11 @@ struct wc_ctx {
   bool have_clov[4] = {false, false, false, false};
   wc::DevBuf clov_eo[4], cscale_eo[4];  // even/odd block solver: A on even, A^-1 on odd sites
   bool have_clov_eo[4] = {false, false, false, false};
+  wc::DevBuf clov_mm[4];  // the matrix-core block solver's clover rows (16-bit storage only)
   wc::DevBuf tiles[2];
   wc::DevBuf eo_sites;                    // [corner parity][site parity][(bvol+1)/2] local indices
   wc::DevBuf eo_slot;                     // [corner parity][bvol] parity-sorted slot of each local site
+  wc::DevBuf eo_nbr, eo_bent, eo_bgat;    // tables of the matrix-core block solver (LatDesc)
   int nr_dirac[4] = {0, 0, 0, 0};
   int nr_sap[4] = {0, 0, 0, 0};
   int nr_sap_eo[4] = {0, 0, 0, 0};
@@ -261,6 +263,11 @@ static void ensure_clover_eo(wc_ctx* c, int prec, hipStream_t st) {
     if (is16(prec)) c->cscale_eo[prec].ensure(sizeof(float) * 2 * c->g.V);
     launch_clover_convert(prec, c->g, c->clov_eo[P_F64].p, c->clov_eo[prec].p, c->cscale_eo[prec].as<float>(), st);
     HIPCK(hipGetLastError());
+    if (is16(prec)) {
+      c->clov_mm[prec].ensure((size_t)c->g.V * SAP_MM_CLOVER_BYTES);
+      launch_clover_mm(c->g.V, c->clov_eo[prec].p, c->clov_mm[prec].p, st);
+      HIPCK(hipGetLastError());
+    }
     c->have_clov_eo[prec] = true;
   }
 }
@@ -375,12 +382,17 @@ struct Batch {
       L.tiles[1] = c->tiles[1].as<int>();
       L.clov_eo = nullptr;
       L.cscale_eo = nullptr;
+      L.clov_mm = nullptr;
       L.eo_sites = c->eo_sites.as<short>();
       L.eo_slot = c->eo_slot.as<short>();
+      L.eo_nbr = c->eo_nbr.as<uint16_t>();
+      L.eo_bent = c->eo_bent.as<uint32_t>();
+      L.eo_bgat = c->eo_bgat.as<uint16_t>();
       if (eo) {
         ensure_clover_eo(c, prec, st);
         L.clov_eo = c->clov_eo[prec].p;
         L.cscale_eo = c->cscale_eo[prec].as<float>();
+        L.clov_mm = c->clov_mm[prec].p;
       }
       h_lats[prec].push_back(L);
       foff += (long long)nrhs[i] * c->g.V;
@@ -435,8 +447,12 @@ struct Batch {
     for (size_t i = 0; i < lat.size(); ++i) {
       if (bvol && lat[i]->g.bvol != bvol) continue;
       const int nt = lat[i]->g.ntiles / 2;
+      // the matrix-core solver's tile costs the same for any number of rhs up to its width:
+      // as equal tiles as possible
+      const int groups = (nrhs[i] + nr - 1) / nr;
+      const int tile = nr == SAP_MM_RHS ? (nrhs[i] + groups - 1) / groups : nr;
       for (int t = 0; t < nt; ++t)
-        for (int r0 = 0; r0 < nrhs[i]; r0 += nr) v.push_back(WorkItem{(int)i, t, r0, std::min(nr, nrhs[i] - r0)});
+        for (int r0 = 0; r0 < nrhs[i]; r0 += tile) v.push_back(WorkItem{(int)i, t, r0, std::min(tile, nrhs[i] - r0)});
     }
     ItemList& L = sap_items[colour][key];
     L.d.ensure(sizeof(WorkItem) * v.size());
@@ -509,6 +525,9 @@ static int default_nr(int nrhs, int prec, bool sap, int eo) {
 
 static int pick_nr(wc_ctx* c, int nrhs, int prec, bool sap, int requested, int eo = 0) {
   int nr = requested > 0 ? requested : (sap ? (eo ? c->nr_sap_eo[prec] : c->nr_sap[prec]) : c->nr_dirac[prec]);
+  // even/odd block solver on 16-bit storage without a tile asked for: the matrix-core kernel
+  // where sap_tile finds it the faster one, per block volume
+  if (nr <= 0 && sap && eo && is16(prec) && nrhs > 1) return SAP_MM_RHS;
   if (nr <= 0) nr = default_nr(nrhs, prec, sap, eo);
   nr = std::min(nr, 4);
   // block-solver tiles keep the LDS exchange buffer within 64 KB: FP64 one rhs, else two
@@ -578,12 +597,50 @@ static int sap_cache_mode(const Batch& B, int nitems) {
 }
 
 
+// largest border entry count of the batch's blocks of volume bv
+static int border_entries_of(const Batch& B, int bv) {
+  int n = 0;
+  for (auto* c : B.lat)
+    if (c->g.bvol == bv) n = std::max(n, border_entry_count(c->g.B));
+  return n;
+}
+
+// The rhs tile of the block solver on the blocks of volume bv: nr, or, where the choice is
+// left (SAP_MM_RHS), the matrix-core kernel or one rhs per work-group of the vector one.
+//
+// One work item of the matrix-core kernel takes the same time for one to four rhs, and with
+// more than 128 sites a work-group has its CU for itself; so it runs in whole rounds over the
+// CUs.  The vector kernel keeps its operator in registers up to two items per CU, and above
+// that shares the CUs evenly.  Measured half-sweeps (us, vector / matrix cores, BF16 storage):
+//   4^4 blocks, one round   71 / 75 (256 blocks, 2 rhs), 85 / 77 (3), 95 / 78 (4)
+//               two rounds  125 / 139 (5 rhs), 139 / 141 (6), 163 / 146 (7), 183 / 148 (8)
+//               1296 blocks 412 / 444 (3 rhs), 510 / 468 (4), 1113 / 1147 (9), 1460 / 1212 (12)
+// that is, a round costs as much as 2.95 items per CU of the vector kernel.  Blocks of at most
+// 128 sites leave room for two work-groups and more on a CU and lanes of the vector kernel
+// idle: 4x3^3 53 / 56 (256 blocks, 4 rhs), 99 / 77 (8); 2x4^3 158 / 80 (512 blocks, 4 rhs);
+// 2^4 545 / 129 (4096 blocks, 4 rhs).
+static int sap_tile(const Batch& B, int nr, int bv) {
+  if (nr != SAP_MM_RHS) return nr;
+  if (sap_eo_mm_lds_bytes(bv, border_entries_of(B, bv)) > LDS_MAX_BYTES) return 1;
+  long long vec = 0, mat = 0;
+  for (size_t i = 0; i < B.lat.size(); ++i) {
+    if (B.lat[i]->g.bvol != bv) continue;
+    const long long blocks = B.lat[i]->g.ntiles / 2;
+    vec += blocks * B.nrhs[i];
+    mat += blocks * ((B.nrhs[i] + SAP_MM_RHS - 1) / SAP_MM_RHS);
+  }
+  const long long cus = device_cus();
+  const bool faster = bv <= 128 ? vec > 4 * cus : vec > 2 * cus && 2.95 * ((mat + cus - 1) / cus) * cus < vec;
+  return faster ? SAP_MM_RHS : 1;
+}
+
 // odd_rho: residual on odd sites for the even/odd solver (see SapLaunch::odd_rho)
 static void run_sap_halfsweep(Batch& B, int prec, int nr, int colour, int nmr, Field& rho, Field& z, Field& psi,
                               const int* skip, int first, int border, int wrho, int wz, int eo, hipStream_t st,
                               int odd_rho = 0) {
-  require(nr >= 1 && nr <= (prec == P_F64 ? 1 : 2), WC_ERR_ARG, "block-solver rhs tile out of range");
-  require((eo ? sap_eo_lds_bytes(prec, nr, B.max_bvol, 0) : sap_lds_bytes(prec, nr, B.sap_threads())) <= 65536,
+  const bool mm_asked = eo && is16(prec) && nr == SAP_MM_RHS;
+  require(mm_asked || (nr >= 1 && nr <= (prec == P_F64 ? 1 : 2)), WC_ERR_ARG, "block-solver rhs tile out of range");
+  require(mm_asked || (eo ? sap_eo_lds_bytes(prec, nr, B.max_bvol, 0) : sap_lds_bytes(prec, nr, B.sap_threads())) <= 65536,
           WC_ERR_GEOMETRY, "block too large for LDS");
   const LatDesc* L = B.lats(prec, st, eo != 0);
   // one launch per block volume of the batch, each with work-groups sized for its own
@@ -591,11 +648,11 @@ static void run_sap_halfsweep(Batch& B, int prec, int nr, int colour, int nmr, F
   for (int bv : B.bvols()) {
     // the even/odd solver's border update runs from LDS entries when they fit a
     // work-group's LDS next to the exchange rows (else per site)
-    int bentries = 0;
-    for (auto* c : B.lat)
-      if (c->g.bvol == bv) bentries = std::max(bentries, border_entry_count(c->g.B));
-    if (eo && sap_eo_lds_bytes(prec, nr, bv, bentries) > LDS_MAX_BYTES) bentries = 0;
-    const ItemList& it = B.items_sap(colour, nr, bv);
+    const int tile = sap_tile(B, nr, bv);
+    const bool mm = tile == SAP_MM_RHS;
+    int bentries = border_entries_of(B, bv);
+    if (eo && !mm && sap_eo_lds_bytes(prec, tile, bv, bentries) > LDS_MAX_BYTES) bentries = 0;
+    const ItemList& it = B.items_sap(colour, tile, bv);
     if (it.n == 0) continue;
     SapLaunch a;
     a.lats = L;
@@ -621,12 +678,15 @@ static void run_sap_halfsweep(Batch& B, int prec, int nr, int colour, int nmr, F
     // extra barrier costs more than the divergent per-site update: measured at 16^3 x 32)
     a.border_entries = (eo && !a.cache) ? bentries : 0;
     a.eo_rows = 2 * ((bv + 1) / 2);
-    if (eo)
-      launch_sap_eo(prec, nr, a, persistent_grid(it.n, 4), bv, st);
-    else if (is16(prec) && nr == 2 && bv == 256)
-      launch_sap_mr_lds(prec, nr, a, persistent_grid(it.n, 1), st);
+    a.mm_xch_bytes = mm ? (int)sap_eo_mm_xch_bytes(bv, bentries) : 0;
+    if (mm)
+      launch_sap_eo_mm(prec, a, bv, bentries, st);
+    else if (eo)
+      launch_sap_eo(prec, tile, a, persistent_grid(it.n, 4), bv, st);
+    else if (is16(prec) && tile == 2 && bv == 256)
+      launch_sap_mr_lds(prec, tile, a, persistent_grid(it.n, 1), st);
     else
-      launch_sap_mr(prec, nr, a, persistent_grid(it.n, 4), ((bv + 63) / 64) * 64, st);
+      launch_sap_mr(prec, tile, a, persistent_grid(it.n, 4), ((bv + 63) / 64) * 64, st);
   }
 }
 
@@ -801,7 +861,7 @@ static void prepare_solver(Batch& B, const SolveSetup& s, bool fgcr = true) {
   for (int nr : {1, s.nr_d, s.nr_d32})
     for (int sel = 0; sel < 3; ++sel) B.items_dirac(nr, sel);
   for (int bv : B.bvols())
-    for (int c = 0; c < 2; ++c) B.items_sap(c, s.nr_s, bv);
+    for (int c = 0; c < 2; ++c) B.items_sap(c, sap_tile(B, s.nr_s, bv), bv);
   HIPCK(hipDeviceSynchronize());
 }
 
@@ -1359,6 +1419,32 @@ static void layout(wc_ctx* c, const int* block, hipStream_t st) {
   HIPCK(hipMemcpy(c->eo_sites.p, lut.data(), sizeof(short) * lut.size(), hipMemcpyHostToDevice));
   c->eo_slot.ensure(sizeof(short) * slot.size());
   HIPCK(hipMemcpy(c->eo_slot.p, slot.data(), sizeof(short) * slot.size(), hipMemcpyHostToDevice));
+  // matrix-core block solver: neighbour slots, border entries and each site's entries
+  const Geom& g = c->g;
+  const int out_slot = 2 * nh;
+  std::vector<uint16_t> nbr(2 * (size_t)g.bvol * 8), gat((size_t)g.bvol * 8, 0xFFFF);
+  std::vector<uint32_t> ent;
+  for (int d = 0; d < 8; ++d) {
+    const int mu = d >> 1, dir = (d & 1) ? -1 : 1;
+    for (int l = 0; l < g.bvol; ++l) {
+      int lc[4];
+      local_coords(g, l, lc);
+      const bool inside = dir > 0 ? lc[mu] + 1 < g.B[mu] : lc[mu] > 0;
+      for (int cp = 0; cp < 2; ++cp)
+        nbr[((size_t)cp * g.bvol + l) * 8 + d] =
+            (uint16_t)(inside ? slot[(size_t)cp * g.bvol + l + dir * g.lstr[mu]] : out_slot);
+      if (inside) continue;
+      const int nl = l - dir * (g.B[mu] - 1) * g.lstr[mu];  // local site across the face
+      gat[(size_t)l * 8 + d] = (uint16_t)ent.size();
+      ent.push_back((uint32_t)l | (uint32_t)nl << 8 | (uint32_t)d << 16);
+    }
+  }
+  c->eo_nbr.ensure(sizeof(uint16_t) * nbr.size());
+  c->eo_bent.ensure(sizeof(uint32_t) * ent.size());
+  c->eo_bgat.ensure(sizeof(uint16_t) * gat.size());
+  HIPCK(hipMemcpy(c->eo_nbr.p, nbr.data(), sizeof(uint16_t) * nbr.size(), hipMemcpyHostToDevice));
+  HIPCK(hipMemcpy(c->eo_bent.p, ent.data(), sizeof(uint32_t) * ent.size(), hipMemcpyHostToDevice));
+  HIPCK(hipMemcpy(c->eo_bgat.p, gat.data(), sizeof(uint16_t) * gat.size(), hipMemcpyHostToDevice));
   for (int p = 0; p < 4; ++p) {
     c->have_links[p] = false;
     c->have_clov[p] = false;
@@ -2024,13 +2110,22 @@ int wc_autotune(wc_ctx* c, int nrhs, int prec, int nr_out[4], void* stream) {
         ne = nr;
       }
     }
+    // even/odd solver with the choice left to the library (several rhs on 16-bit storage: the
+    // matrix-core kernel by sap_tile's rule)
+    if (nrhs > 1 && is16(prec)) {
+      double t = 0;
+      c->nr_sap_eo[prec] = 0;
+      const int rc = wc_bench_sap(c, prec, nrhs, 4, 1, 10, &t, stream);
+      require(rc == WC_OK, rc, g_last_error);
+      if (t < best_e) ne = 0;
+    }
     c->nr_sap[prec] = ns;
     c->nr_sap_eo[prec] = ne;
     if (nr_out) {
       nr_out[0] = c->nr_dirac[prec];
       nr_out[1] = c->nr_dirac[P_F64];
       nr_out[2] = ns;
-      nr_out[3] = ne;
+      nr_out[3] = std::max(ne, 1);
     }
   });
 }

@@ -27,6 +27,13 @@ struct LatDesc {
   const float* cscale_eo; // its 16-bit scales [V][2]
   const short* eo_sites;  // [corner parity][site parity][(bvol+1)/2] tile-local site indices, -1 = none
   const short* eo_slot;   // [corner parity][bvol] slot of each tile-local site in the parity-sorted order
+  // matrix-core block solver
+  const uint16_t* eo_nbr;  // [corner parity][bvol][4][2] slots of the forward / backward neighbours
+                           // along each direction (2 * ((bvol + 1) / 2): outside the block)
+  const uint32_t* eo_bent; // border entries: tile-local site | neighbour's local site << 8 |
+                           // (2 * direction + backward) << 16
+  const void* clov_mm;     // rows of the even/odd clover blocks (16-bit storage, see sap_eo_mm.hip)
+  const uint16_t* eo_bgat; // [bvol][4][2] a site's border entry of each face (0xFFFF: none)
 };
 
 // A unit of work: WG consecutive sites (or one tile for the Schwarz kernels)

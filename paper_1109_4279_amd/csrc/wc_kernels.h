@@ -77,6 +77,7 @@ struct SapLaunch {
   // rows of length eo_rows
   int border_entries;
   int eo_rows;
+  int mm_xch_bytes;  // matrix-core solver: LDS bytes of its exchange slots
 };
 void launch_sap_mr(int prec, int nr, const SapLaunch& a, int grid, int block_threads, hipStream_t st);
 size_t sap_lds_bytes(int prec, int nr, int bvol);
@@ -88,6 +89,15 @@ void launch_sap_eo(int prec, int nr, const SapLaunch& a, int grid, int max_bvol,
 // dynamic LDS of the even/odd solver: reduction scratch, the exchange rows and, when
 // border_entries > 0, the border update's entries
 size_t sap_eo_lds_bytes(int prec, int nr, int max_bvol, int border_entries);
+// the same solver for several rhs per work-group (up to SAP_MM_RHS) on the matrix cores,
+// 16-bit storage: LDS bytes of its exchange slots (or border entries) and in all
+constexpr int SAP_MM_RHS = 4;
+size_t sap_eo_mm_xch_bytes(int bvol, int border_entries);
+size_t sap_eo_mm_lds_bytes(int bvol, int border_entries);
+// its clover operand from the 16-bit even/odd clover field: SAP_MM_CLOVER_BYTES per site
+constexpr size_t SAP_MM_CLOVER_BYTES = 8 * 9 * 4;
+void launch_clover_mm(int V, const void* clov_eo16, void* dst, hipStream_t st);
+void launch_sap_eo_mm(int prec, const SapLaunch& a, int bvol, int border_entries, hipStream_t st);
 // cross-block hops of one block (the border update's entries): two faces per direction
 WC_HD int border_entry_count(const int* B) {
   const int vol = B[0] * B[1] * B[2] * B[3];
