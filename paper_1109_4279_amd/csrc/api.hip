@@ -79,10 +79,69 @@ static hipGraphExec_t capture_graph(hipStream_t cap, const std::function<void(hi
   return exec;
 }
 
+// Device memory of destroyed contexts and finished calls, kept for the next ones: a program
+// that builds a context per gauge field (a molecular-dynamics step, a differentiated
+// application) otherwise spends longer in hipMalloc and hipFree than in its kernels (12^3 x 24
+// dirac_apply and its gradients: 1.39 ms a call with them, 0.45 ms of kernels).  A block enters
+// the pool only when no work on any stream can still use it (its giver has waited for that),
+// so whoever takes it next, on any stream or thread, may write it at once.  At most POOL_BYTES
+// per device are kept, the rest goes back to the runtime; an allocation that fails empties the
+// device's pool and is tried again.
+constexpr size_t POOL_BYTES = size_t(2) << 30;
+
+struct DevPool {
+  struct Dev {
+    std::multimap<size_t, void*> blocks;
+    size_t bytes = 0;
+  };
+  std::mutex mu;
+  std::map<int, Dev> devs;
+
+  // a kept block of at least `bytes` and at most a quarter more, or null
+  void* take(int dev, size_t bytes, size_t* got) {
+    std::lock_guard<std::mutex> lock(mu);
+    Dev& d = devs[dev];
+    auto it = d.blocks.lower_bound(bytes);
+    if (it == d.blocks.end() || it->first > bytes + bytes / 4 + 4096) return nullptr;
+    void* p = it->second;
+    *got = it->first;
+    d.bytes -= it->first;
+    d.blocks.erase(it);
+    return p;
+  }
+  // false: the pool is full, the caller frees the block
+  bool give(int dev, void* p, size_t bytes) {
+    std::lock_guard<std::mutex> lock(mu);
+    Dev& d = devs[dev];
+    if (d.bytes + bytes > POOL_BYTES) return false;
+    d.blocks.emplace(bytes, p);
+    d.bytes += bytes;
+    return true;
+  }
+  void empty(int dev) {
+    std::multimap<size_t, void*> blocks;
+    {
+      std::lock_guard<std::mutex> lock(mu);
+      Dev& d = devs[dev];
+      blocks.swap(d.blocks);
+      d.bytes = 0;
+    }
+    for (auto& kv : blocks) (void)hipFree(kv.second);
+  }
+};
+
+// On the heap and never freed: blocks kept at the end of the process go with it, not after
+// the runtime.
+static DevPool& dev_pool() {
+  static auto* p = new DevPool();
+  return *p;
+}
+
 // owning device allocation
 struct DevBuf {
   void* p = nullptr;
   size_t n = 0;
+  int dev = -1;
   DevBuf() = default;
   DevBuf(const DevBuf&) = delete;
   DevBuf& operator=(const DevBuf&) = delete;
@@ -92,10 +151,26 @@ struct DevBuf {
     p = nullptr;
     n = 0;
   }
+  // Gives the memory to the pool.  The caller has waited for all work that uses it.
+  void recycle() {
+    if (p && dev_pool().give(dev, p, n)) p = nullptr;
+    release();
+  }
   void ensure(size_t bytes) {
     if (bytes <= n && p) return;
     release();
-    HIPCK(hipMalloc(&p, bytes ? bytes : 16));
+    if (bytes < 16) bytes = 16;
+    HIPCK(hipGetDevice(&dev));
+    p = dev_pool().take(dev, bytes, &n);
+    if (p) return;
+    hipError_t e = hipMalloc(&p, bytes);
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      dev_pool().empty(dev);
+      e = hipMalloc(&p, bytes);
+    }
+    if (e != hipSuccess) p = nullptr;
+    HIPCK(e);
     n = bytes;
   }
   template <class T> T* as() const { return (T*)p; }
@@ -214,10 +289,15 @@ struct wc_ctx {
   wc::DevBuf clov_eo[4], cscale_eo[4];  // even/odd block solver: A on even, A^-1 on odd sites
   bool have_clov_eo[4] = {false, false, false, false};
   wc::DevBuf clov_mm[4];  // the matrix-core block solver's clover rows (16-bit storage only)
-  wc::DevBuf tiles[2];
-  wc::DevBuf eo_sites;                    // [corner parity][site parity][(bvol+1)/2] local indices
-  wc::DevBuf eo_slot;                     // [corner parity][bvol] parity-sorted slot of each local site
-  wc::DevBuf eo_nbr, eo_bent, eo_bgat;    // tables of the matrix-core block solver (LatDesc)
+  // layout tables, one allocation and one copy: tile lists of the two colours, and the block
+  // solvers' (LatDesc)
+  wc::DevBuf tables;
+  const int* tiles[2] = {nullptr, nullptr};
+  const short* eo_sites = nullptr;  // [corner parity][site parity][(bvol+1)/2] local indices
+  const short* eo_slot = nullptr;   // [corner parity][bvol] parity-sorted slot of each local site
+  const uint16_t* eo_nbr = nullptr;
+  const uint32_t* eo_bent = nullptr;
+  const uint16_t* eo_bgat = nullptr;
   int nr_dirac[4] = {0, 0, 0, 0};
   int nr_sap[4] = {0, 0, 0, 0};
   int nr_sap_eo[4] = {0, 0, 0, 0};
@@ -378,16 +458,16 @@ struct Batch {
       L.sys0 = sys0;
       L.part0 = part0;
       L.nchunks = (c->g.V + WG - 1) / WG;
-      L.tiles[0] = c->tiles[0].as<int>();
-      L.tiles[1] = c->tiles[1].as<int>();
+      L.tiles[0] = c->tiles[0];
+      L.tiles[1] = c->tiles[1];
       L.clov_eo = nullptr;
       L.cscale_eo = nullptr;
       L.clov_mm = nullptr;
-      L.eo_sites = c->eo_sites.as<short>();
-      L.eo_slot = c->eo_slot.as<short>();
-      L.eo_nbr = c->eo_nbr.as<uint16_t>();
-      L.eo_bent = c->eo_bent.as<uint32_t>();
-      L.eo_bgat = c->eo_bgat.as<uint16_t>();
+      L.eo_sites = c->eo_sites;
+      L.eo_slot = c->eo_slot;
+      L.eo_nbr = c->eo_nbr;
+      L.eo_bent = c->eo_bent;
+      L.eo_bgat = c->eo_bgat;
       if (eo) {
         ensure_clover_eo(c, prec, st);
         L.clov_eo = c->clov_eo[prec].p;
@@ -1397,10 +1477,6 @@ static void layout(wc_ctx* c, const int* block, hipStream_t st) {
     tile_coords(c->g, t, tc);
     (tile_colour(tc) ? t1 : t0).push_back(t);
   }
-  c->tiles[0].ensure(sizeof(int) * t0.size());
-  c->tiles[1].ensure(sizeof(int) * t1.size());
-  HIPCK(hipMemcpy(c->tiles[0].p, t0.data(), sizeof(int) * t0.size(), hipMemcpyHostToDevice));
-  HIPCK(hipMemcpy(c->tiles[1].p, t1.data(), sizeof(int) * t1.size(), hipMemcpyHostToDevice));
   // even and odd sites of a tile in local order, for both parities of the tile's corner
   const int nh = (c->g.bvol + 1) / 2;
   // and each site's slot when the even sites come first, then the odd ones, in that order
@@ -1415,10 +1491,6 @@ static void layout(wc_ctx* c, const int* block, hipStream_t st) {
       lut[(size_t)(2 * cp + par) * nh + cnt[par]++] = (short)l;
     }
   }
-  c->eo_sites.ensure(sizeof(short) * lut.size());
-  HIPCK(hipMemcpy(c->eo_sites.p, lut.data(), sizeof(short) * lut.size(), hipMemcpyHostToDevice));
-  c->eo_slot.ensure(sizeof(short) * slot.size());
-  HIPCK(hipMemcpy(c->eo_slot.p, slot.data(), sizeof(short) * slot.size(), hipMemcpyHostToDevice));
   // matrix-core block solver: neighbour slots, border entries and each site's entries
   const Geom& g = c->g;
   const int out_slot = 2 * nh;
@@ -1439,12 +1511,28 @@ static void layout(wc_ctx* c, const int* block, hipStream_t st) {
       ent.push_back((uint32_t)l | (uint32_t)nl << 8 | (uint32_t)d << 16);
     }
   }
-  c->eo_nbr.ensure(sizeof(uint16_t) * nbr.size());
-  c->eo_bent.ensure(sizeof(uint32_t) * ent.size());
-  c->eo_bgat.ensure(sizeof(uint16_t) * gat.size());
-  HIPCK(hipMemcpy(c->eo_nbr.p, nbr.data(), sizeof(uint16_t) * nbr.size(), hipMemcpyHostToDevice));
-  HIPCK(hipMemcpy(c->eo_bent.p, ent.data(), sizeof(uint32_t) * ent.size(), hipMemcpyHostToDevice));
-  HIPCK(hipMemcpy(c->eo_bgat.p, gat.data(), sizeof(uint16_t) * gat.size(), hipMemcpyHostToDevice));
+  std::vector<char> host;
+  auto put = [&](const void* data, size_t bytes) {
+    const size_t at = (host.size() + 15) / 16 * 16;
+    host.resize(at + bytes);
+    std::memcpy(host.data() + at, data, bytes);
+    return at;
+  };
+  const size_t o_t0 = put(t0.data(), sizeof(int) * t0.size()), o_t1 = put(t1.data(), sizeof(int) * t1.size());
+  const size_t o_lut = put(lut.data(), sizeof(short) * lut.size()), o_slot = put(slot.data(), sizeof(short) * slot.size());
+  const size_t o_nbr = put(nbr.data(), sizeof(uint16_t) * nbr.size());
+  const size_t o_ent = put(ent.data(), sizeof(uint32_t) * ent.size());
+  const size_t o_gat = put(gat.data(), sizeof(uint16_t) * gat.size());
+  c->tables.ensure(host.size());
+  HIPCK(hipMemcpy(c->tables.p, host.data(), host.size(), hipMemcpyHostToDevice));
+  const char* base = c->tables.as<char>();
+  c->tiles[0] = (const int*)(base + o_t0);
+  c->tiles[1] = (const int*)(base + o_t1);
+  c->eo_sites = (const short*)(base + o_lut);
+  c->eo_slot = (const short*)(base + o_slot);
+  c->eo_nbr = (const uint16_t*)(base + o_nbr);
+  c->eo_bent = (const uint32_t*)(base + o_ent);
+  c->eo_bgat = (const uint16_t*)(base + o_gat);
   for (int p = 0; p < 4; ++p) {
     c->have_links[p] = false;
     c->have_clov[p] = false;
@@ -1465,6 +1553,18 @@ wc_ctx::~wc_ctx() {
   batches.clear();
   wc::drop_multi_batches(this);
   if (cap) (void)hipStreamDestroy(cap);
+  // Once nothing on the device can still use them, the context's own buffers go to the pool
+  // (if the wait fails, hipFree waits for them one by one).
+  int cur = -1;
+  if (hipGetDevice(&cur) != hipSuccess || cur != dev || hipDeviceSynchronize() != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  Ucanon.recycle();
+  tables.recycle();
+  for (int p = 0; p < 4; ++p)
+    for (wc::DevBuf* b : {&links[p], &lscale[p], &clov[p], &cscale[p], &clov_eo[p], &cscale_eo[p], &clov_mm[p]})
+      b->recycle();
 }
 
 using namespace wc;
@@ -1678,10 +1778,10 @@ int wc_apply_D_noalloc(wc_ctx* c, void* out, const void* in, int nrhs, int prec,
     L.foff = 0;
     L.nrhs = nrhs;
     L.nchunks = nch;
-    L.tiles[0] = c->tiles[0].as<int>();
-    L.tiles[1] = c->tiles[1].as<int>();
-    L.eo_sites = c->eo_sites.as<short>();
-    L.eo_slot = c->eo_slot.as<short>();
+    L.tiles[0] = c->tiles[0];
+    L.tiles[1] = c->tiles[1];
+    L.eo_sites = c->eo_sites;
+    L.eo_slot = c->eo_slot;
     LatDesc* d_lat = (LatDesc*)base;
     WorkItem* d_items = (WorkItem*)(base + items_off);
     hipLaunchKernelGGL(k_noalloc_tables, dim3((unsigned)std::min<long long>((nitems + 255) / 256, 1024)), dim3(256), 0,
@@ -1908,6 +2008,7 @@ int wc_link_grad(wc_ctx* c, void* G, const void* Y, const void* X, int nrhs, dou
                  S(stream));
     HIPCK(hipGetLastError());
     HIPCK(hipStreamSynchronize(S(stream)));
+    xi.recycle();
   });
 }
 
@@ -1949,6 +2050,7 @@ int wc_force(wc_ctx* c, void* F, const void* phi, const wc_solver_params* p, wc_
     if (Yout) HIPCK(hipMemcpyAsync(Yout, y.p, bytes, hipMemcpyDeviceToDevice, st_));
     if (Xout) HIPCK(hipMemcpyAsync(Xout, x.p, bytes, hipMemcpyDeviceToDevice, st_));
     HIPCK(hipStreamSynchronize(st_));
+    for (DevBuf* b : {&y, &x, &tmp, &xi}) b->recycle();
     if (st) {
       st[0] = s2[0];
       st[1] = s2[1];
@@ -1973,6 +2075,8 @@ int wc_pseudofermion_action(wc_ctx* c, const void* phi, const wc_solver_params* 
     HIPCK(hipGetLastError());
     HIPCK(hipMemcpyAsync(Sout, work.p, sizeof(double), hipMemcpyDeviceToHost, st_));
     HIPCK(hipStreamSynchronize(st_));
+    tmp.recycle();
+    work.recycle();
     if (st) {
       st[0] = s2[0];
       st[1] = s2[1];
