@@ -18,8 +18,8 @@
 
 namespace wc {
 
-void launch_force(const int* L, int bc_t, const void* Ucanon, const void* Y, const void* X, int nrhs, double csw,
-                  double coef, int out_kind, void* xi_work, void* out, hipStream_t st);
+void launch_force(const Geom& g, const void* links64, const void* Y, const void* X, int nrhs, double csw, double coef,
+                  int out_kind, void* xi_work, void* out, hipStream_t st);
 void launch_gamma5_canon(long long nsite, const void* src, void* dst, hipStream_t st);
 void launch_gamma5_f64(void* f, long long V, int nrhs, hipStream_t st);
 void launch_clover_export(const Geom& g, const void* c64, void* out, hipStream_t st);
@@ -2004,8 +2004,7 @@ int wc_link_grad(wc_ctx* c, void* G, const void* Y, const void* X, int nrhs, dou
     require(c && G && Y && X && nrhs >= 1, WC_ERR_ARG, "bad argument");
     DevBuf xi;
     if (c->csw != 0.0) xi.ensure(sizeof(double2) * 54 * (size_t)c->g.V);
-    launch_force(c->dims, c->bc_t, c->Ucanon.p, Y, X, nrhs, c->have_clover ? c->csw : 0.0, coef, 0, xi.p, G,
-                 S(stream));
+    launch_force(c->g, c->links[P_F64].p, Y, X, nrhs, c->have_clover ? c->csw : 0.0, coef, 0, xi.p, G, S(stream));
     HIPCK(hipGetLastError());
     HIPCK(hipStreamSynchronize(S(stream)));
     xi.recycle();
@@ -2045,7 +2044,7 @@ int wc_force(wc_ctx* c, void* F, const void* phi, const wc_solver_params* p, wc_
     rc_solve = action_solves(c, phi, p, y.p, x.p, tmp.p, s2, stream);
     DevBuf xi;
     if (c->csw != 0.0) xi.ensure(sizeof(double2) * 54 * (size_t)c->g.V);
-    launch_force(c->dims, c->bc_t, c->Ucanon.p, y.p, x.p, 1, c->csw, 1.0, 1, xi.p, F, st_);
+    launch_force(c->g, c->links[P_F64].p, y.p, x.p, 1, c->csw, 1.0, 1, xi.p, F, st_);
     HIPCK(hipGetLastError());
     if (Yout) HIPCK(hipMemcpyAsync(Yout, y.p, bytes, hipMemcpyDeviceToDevice, st_));
     if (Xout) HIPCK(hipMemcpyAsync(Xout, x.p, bytes, hipMemcpyDeviceToDevice, st_));

@@ -248,10 +248,4 @@ void launch_arn_update(const VecLaunch& a, int grid, hipStream_t st);
 // V_l <- sum_i P_il V_i (l < pout, i < pin), Z_l <- sum_i P_il Z_i (l < pout-1, i < pin-1), in place
 void launch_arn_recombine(const VecLaunch& a, int grid, hipStream_t st);
 
-// ----------------------------------------------------------------- force
-// K_mu(x) += coef * d Re<Y, D X>/dU (torch convention: G = K^dag) per link, canonical [4][V][3][3]
-void launch_link_grad(const Geom& g, const void* links64, const void* Y, const void* X, int nrhs, double csw,
-                      double coef, void* Kout, hipStream_t st);
-void launch_lie_force(const Geom& g, const void* links64, const void* K, void* F, hipStream_t st);
-
 }  // namespace wc
