@@ -692,13 +692,13 @@ static int border_entries_of(const Batch& B, int bv) {
 // more than 128 sites a work-group has its CU for itself; so it runs in whole rounds over the
 // CUs.  The vector kernel keeps its operator in registers up to two items per CU, and above
 // that shares the CUs evenly.  Measured half-sweeps (us, vector / matrix cores, BF16 storage):
-//   4^4 blocks, one round   71 / 75 (256 blocks, 2 rhs), 85 / 77 (3), 95 / 78 (4)
-//               two rounds  125 / 139 (5 rhs), 139 / 141 (6), 163 / 146 (7), 183 / 148 (8)
-//               1296 blocks 412 / 444 (3 rhs), 510 / 468 (4), 1113 / 1147 (9), 1460 / 1212 (12)
-// that is, a round costs as much as 2.95 items per CU of the vector kernel.  Blocks of at most
+//   4^4 blocks, one round   71 / 70 (256 blocks, 2 rhs), 85 / 68 (3), 96 / 70 (4)
+//               two rounds  138 / 125 (6 rhs), 164 / 127 (7), 182 / 133 (8); 124 (5 rhs, vector)
+//               1296 blocks 415 / 402 (3 rhs), 511 / 410 (4), 877 / 720 (7), 1461 / 1070 (12)
+// that is, a round costs as much as 2.7 items per CU of the vector kernel.  Blocks of at most
 // 128 sites leave room for two work-groups and more on a CU and lanes of the vector kernel
-// idle: 4x3^3 53 / 56 (256 blocks, 4 rhs), 99 / 77 (8); 2x4^3 158 / 80 (512 blocks, 4 rhs);
-// 2^4 545 / 129 (4096 blocks, 4 rhs).
+// idle: 4x3^3 98 / 67 (256 blocks, 8 rhs; 4 rhs 53 / 56); 2x4^3 159 / 68 (512 blocks, 4 rhs);
+// 2^4 550 / 111 (4096 blocks, 4 rhs).
 static int sap_tile(const Batch& B, int nr, int bv) {
   if (nr != SAP_MM_RHS) return nr;
   if (sap_eo_mm_lds_bytes(bv, border_entries_of(B, bv)) > LDS_MAX_BYTES) return 1;
@@ -710,7 +710,7 @@ static int sap_tile(const Batch& B, int nr, int bv) {
     mat += blocks * ((B.nrhs[i] + SAP_MM_RHS - 1) / SAP_MM_RHS);
   }
   const long long cus = device_cus();
-  const bool faster = bv <= 128 ? vec > 4 * cus : vec > 2 * cus && 2.95 * ((mat + cus - 1) / cus) * cus < vec;
+  const bool faster = bv <= 128 ? vec > 4 * cus : vec > 2 * cus && 2.7 * ((mat + cus - 1) / cus) * cus < vec;
   return faster ? SAP_MM_RHS : 1;
 }
 

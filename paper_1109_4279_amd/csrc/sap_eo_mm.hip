@@ -16,12 +16,12 @@
 //
 // What bounds it: issue.  k_sap_eo issues 1957 vector instructions per wavefront of 64
 // (site, rhs) and MR step, two thirds of them the FMAs of these products and the decoding of
-// the operator per rhs; here a wavefront issues 1257 vector and 576 matrix instructions for 128
-// of them.  (A 4x4x1 matrix instruction holds the SIMD for 8 cycles, in which no vector
-// instruction of another wavefront was seen to issue.)  The MR steps run at 70 % of that
-// bound with two wavefronts per SIMD.  24^3 x 48, 12 rhs, BF16: half-sweep 1460 (k_sap_eo) ->
-// 1212 us, of it set-up and stores 514 us, an MR step 175 us (214 us); the batched solve of 12
-// point sources 309 -> 255 ms.
+// the operator per rhs; here a wavefront issues 1276 vector and 576 matrix instructions for 128
+// of them.  A 4x4x1 matrix instruction holds its SIMD for 8 cycles, and vector instructions do
+// not run beside it; with two wavefronts per SIMD the MR steps take 22 000 cycles against
+// 19 400 of issue.  24^3 x 48, 12 rhs, BF16: half-sweep 1460 (k_sap_eo) -> 1067 us, of it
+// set-up and stores 507 us, an MR step 140 us (214 us).  (With the matrix instructions in runs
+// of 24 instead of 48, see mm_hops, and the field addresses spilled over the MR loop: 1213 us.)
 //
 // Operator: the block's links are staged in LDS once (9 packed words each); the lane's rows
 // of the two clover blocks of its two sites are kept packed in registers (48 words).  The
@@ -41,7 +41,6 @@ namespace wc {
 constexpr int MM_SLOT = 448;       // bytes of an exchange slot: [6][4 rhs] float4 and padding
 constexpr int MM_ENT = 192;        // bytes of a border entry: [3][4 rhs] float4
 constexpr int MM_MAX_WAVES = 8;
-constexpr int MM_ROUNDS = 4;       // rounds of border entries in flight together (all of a 4^4 block's)
 
 typedef float mf4 __attribute__((ext_vector_type(4)));
 
@@ -162,36 +161,33 @@ WC_D Spinor<float> mm_hops(const char* xch, const uint32_t* lk, const float* lsc
   Spinor<float> acc;
   zero(acc);
   const float w_own = wt * lsc[own];
+  // Both hops of a direction are projected, multiplied and reconstructed together: matrix and
+  // vector instructions that alternate on a SIMD, of one wavefront or of two, cost about 9
+  // cycles more per alternation than one after the other, so the matrix instructions come in
+  // runs of 48.  (Measured: 24 matrix + 48 vector instructions in turn on two wavefronts 1037
+  // cycles, 48 + 96 in turn 900 for the same work, the sum of the parts 864.)
   auto dir = [&](auto MUc) {
     constexpr int MU = decltype(MUc)::value;
     const int sf = nb[MU] & 0xFFFFu, sb = nb[MU] >> 16;
-    {
-      const uint32_t* l = lk + (MU * lrow + own) * 9 + 3 * jr;
-      const uint32_t w[3] = {l[0], l[1], l[2]};
-      MRow m;
-      unpack_row<P>(w, m);
-      const Spinor<float> p = slot_read(xch + sf * MM_SLOT + 16 * j);
-      recon_fma<MU, -1>(acc, mm_half(m, project<float, MU, -1>(p)), w_own);
-    }
-    {
-      // rows of U^dag: the columns of U, conjugated
-      const uint32_t* l = lk + (MU * lrow + sb) * 9 + jr;
-      const uint32_t w[3] = {l[0], l[3], l[6]};
-      MRow m;
-      unpack_row<P, true>(w, m);
-      const Spinor<float> p = slot_read(xch + sb * MM_SLOT + 16 * j);
-      const float wb = wt * lsc[sb];
-      recon_fma<MU, +1>(acc, mm_half(m, project<float, MU, +1>(p)), wb);
-    }
+    const uint32_t* lf = lk + (MU * lrow + own) * 9 + 3 * jr;
+    const uint32_t* lb = lk + (MU * lrow + sb) * 9 + jr;  // rows of U^dag: columns of U, conjugated
+    const uint32_t wf[3] = {lf[0], lf[1], lf[2]}, wb[3] = {lb[0], lb[3], lb[6]};
+    MRow mf, mb;
+    const Half<float> hf = project<float, MU, -1>(slot_read(xch + sf * MM_SLOT + 16 * j));
+    const Half<float> hb = project<float, MU, +1>(slot_read(xch + sb * MM_SLOT + 16 * j));
+    const float w_b = wt * lsc[sb];
+    unpack_row<P>(wf, mf);
+    unpack_row<P, true>(wb, mb);
+    __builtin_amdgcn_sched_barrier(0);
+    const Half<float> tf = mm_half(mf, hf), tb = mm_half(mb, hb);
+    __builtin_amdgcn_sched_barrier(0);
+    recon_fma<MU, -1>(acc, tf, w_own);
+    recon_fma<MU, +1>(acc, tb, w_b);
+    __builtin_amdgcn_sched_barrier(0);
   };
-  // (the directions one after the other: the reads of all eight hops ahead of their products
-  // would not fit the registers)
   dir(std::integral_constant<int, 0>());
-  __builtin_amdgcn_sched_barrier(0);
   dir(std::integral_constant<int, 1>());
-  __builtin_amdgcn_sched_barrier(0);
   dir(std::integral_constant<int, 2>());
-  __builtin_amdgcn_sched_barrier(0);
   dir(std::integral_constant<int, 3>());
   return acc;
 }
@@ -234,19 +230,24 @@ WC_D void keep_packed(ClRows& c) {
 template <int P> WC_D Spinor<float> mm_clover(const ClRows& c, const Spinor<float>& v) {
   Spinor<float> o;
 #pragma unroll
-  for (int b = 0; b < 2; ++b)
+  for (int b = 0; b < 2; ++b) {
+    MRow m[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) unpack_row<P>(c.w[b][i], m[i]);
+    __builtin_amdgcn_sched_barrier(0);
+    mf4 cre[2], cim[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      mf4 cre = {0.f, 0.f, 0.f, 0.f}, cim = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        MRow m;
-        unpack_row<P>(c.w[b][2 * s + t], m);
-        mm3(m, v.c[2 * b + t], cre, cim);
-      }
-#pragma unroll
-      for (int a = 0; a < 3; ++a) o.c[2 * b + s][a] = {cre[a], cim[a]};
+      cre[s] = cim[s] = mf4{0.f, 0.f, 0.f, 0.f};
+      mm3(m[2 * s], v.c[2 * b], cre[s], cim[s]);
+      mm3(m[2 * s + 1], v.c[2 * b + 1], cre[s], cim[s]);
     }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int a = 0; a < 3; ++a) o.c[2 * b + s][a] = {cre[s][a], cim[s][a]};
+  }
   return o;
 }
 
@@ -302,11 +303,13 @@ __global__ __launch_bounds__(64 * MM_MAX_WAVES, 2) void k_sap_eo_mm(SapLaunch a)
   }
   const bool live = j < w.nr;
   const bool store = live && !(a.skip && a.skip[L.sys0 + w.rhs0 + (live ? j : 0)]);
-  const long long off = L.foff + (long long)(w.rhs0 + (live ? j : 0)) * g.V;
-  constexpr int sb = 48;
-  const FieldRef frho{(char*)a.rho + off * sb, a.rho_sc + off, g.V};
-  const FieldRef fz{(char*)a.z + off * sb, a.z_sc + off, g.V};
-  const FieldRef fpsi{(char*)a.psi + off * sb, a.psi_sc + off, g.V};
+  // this lane's rhs in a field
+  auto field = [&](void* d, float* sc, int lane_rhs) {
+    const long long off = L.foff + (long long)(w.rhs0 + lane_rhs) * g.V;
+    return FieldRef{(char*)d + off * 48, sc + off, g.V};
+  };
+  const FieldRef frho = field(a.rho, a.rho_sc, live ? j : 0);
+  const FieldRef fz = field(a.z, a.z_sc, live ? j : 0);
 
   // Everything the set-up reads is requested before the first use (one work-group per CU
   // leaves nothing else to cover the latency): residual, links and clover rows.
@@ -330,16 +333,12 @@ __global__ __launch_bounds__(64 * MM_MAX_WAVES, 2) void k_sap_eo_mm(SapLaunch a)
   }
   if (threadIdx.x < 4 * 9) lk[((threadIdx.x / 9) * lrow + ls) * 9 + threadIdx.x % 9] = 0;
   if (threadIdx.x == 0) lsc[ls] = 0.f;
-  ClRows ce, co;
-  clover_rows(L, so, jr, co);
-  clover_rows(L, se, jr, ce);
-
   // bring the residual up to date with the other colour's latest block solutions
   if (a.border) {
     const uint4 gte = gld_u4(L.eo_bgat, lel), gto = gld_u4(L.eo_bgat, lol);
     const int ne = border_entry_count(g.B);
     const int rounds = (ne + 16 * nwaves - 1) / (16 * nwaves);
-    constexpr int UN = MM_ROUNDS;
+    constexpr int UN = 4;  // rounds whose loads are in flight together (all of a 4^4 block's)
     for (int rd = 0; rd < rounds; rd += UN) {
       uint32_t rw[UN][3], dd[UN];
       uint4 raw[UN][3];
@@ -374,28 +373,36 @@ __global__ __launch_bounds__(64 * MM_MAX_WAVES, 2) void k_sap_eo_mm(SapLaunch a)
         dd[u] = d;
       }
 #pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        const int e = ((rd + u) * nwaves + wave) * 16 + (lane >> 2);
-        const Spinor<float> p = unpack_spinor<P>(raw[u]);
-        Half<float> h;
-        switch (dd[u]) {
-          case 0: h = project<float, 0, -1>(p); break;
-          case 1: h = project<float, 0, +1>(p); break;
-          case 2: h = project<float, 1, -1>(p); break;
-          case 3: h = project<float, 1, +1>(p); break;
-          case 4: h = project<float, 2, -1>(p); break;
-          case 5: h = project<float, 2, +1>(p); break;
-          case 6: h = project<float, 3, -1>(p); break;
-          default: h = project<float, 3, +1>(p); break;
+      for (int v = 0; v < UN; v += 2) {  // two rounds' products together
+        Half<float> h[UN];
+        MRow m[UN];
+#pragma unroll
+        for (int u = v; u < v + 2; ++u) {
+          const Spinor<float> p = unpack_spinor<P>(raw[u]);
+          switch (dd[u]) {
+            case 0: h[u] = project<float, 0, -1>(p); break;
+            case 1: h[u] = project<float, 0, +1>(p); break;
+            case 2: h[u] = project<float, 1, -1>(p); break;
+            case 3: h[u] = project<float, 1, +1>(p); break;
+            case 4: h[u] = project<float, 2, -1>(p); break;
+            case 5: h[u] = project<float, 2, +1>(p); break;
+            case 6: h[u] = project<float, 3, -1>(p); break;
+            default: h[u] = project<float, 3, +1>(p); break;
+          }
+          unpack_row<P>(rw[u], m[u]);
         }
-        MRow m;
-        unpack_row<P>(rw[u], m);
-        const Half<float> t = mm_half(m, h);
-        if (e < ne) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = v; u < v + 2; ++u) h[u] = mm_half(m[u], h[u]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = v; u < v + 2; ++u) {
+          const int e = ((rd + u) * nwaves + wave) * 16 + (lane >> 2);
+          if (e >= ne) continue;
           char* q = xch + (size_t)e * MM_ENT + 16 * j;
 #pragma unroll
           for (int k = 0; k < 3; ++k) {
-            const cplx<float> x = t.c[(2 * k) / 3][(2 * k) % 3], y = t.c[(2 * k + 1) / 3][(2 * k + 1) % 3];
+            const cplx<float> x = h[u].c[(2 * k) / 3][(2 * k) % 3], y = h[u].c[(2 * k + 1) / 3][(2 * k + 1) % 3];
             *(mf4*)(q + 64 * k) = mf4{wgt[u] * x.re, wgt[u] * x.im, wgt[u] * y.re, wgt[u] * y.im};
           }
         }
@@ -431,6 +438,9 @@ __global__ __launch_bounds__(64 * MM_MAX_WAVES, 2) void k_sap_eo_mm(SapLaunch a)
     __syncthreads();  // the entries' space becomes the exchange slots
   }
 
+  ClRows ce, co;
+  clover_rows(L, so, jr, co);
+  clover_rows(L, se, jr, ce);
   for (int i = threadIdx.x; i < MM_SLOT / 4; i += blockDim.x) ((float*)(xch + ls * MM_SLOT))[i] = 0.f;
 
   // z_o = A_oo^-1 eta_o to start with; source of the Schur system: eta_e - H_eo z_o
@@ -518,6 +528,10 @@ __global__ __launch_bounds__(64 * MM_MAX_WAVES, 2) void k_sap_eo_mm(SapLaunch a)
   }
 
   if (!store) return;
+  // (the field addresses anew: kept from the set-up they would spill over the MR loop)
+  int jl = j;
+  asm volatile("" : "+v"(jl));
+  const FieldRef orho = field(a.rho, a.rho_sc, jl), oz = field(a.z, a.z_sc, jl), fpsi = field(a.psi, a.psi_sc, jl);
   Spinor<float> pe, po;
   zero(pe);
   zero(po);
@@ -526,8 +540,8 @@ __global__ __launch_bounds__(64 * MM_MAX_WAVES, 2) void k_sap_eo_mm(SapLaunch a)
     po = SpinorIO<P>::load(fpsi, so);
   }
   auto put = [&](int site, const Spinor<float>& z, const Spinor<float>& res, const Spinor<float>& psi, bool wr) {
-    if (wr) SpinorIO<P>::store(frho, site, res);
-    if (a.write_z) SpinorIO<P>::store(fz, site, z);
+    if (wr) SpinorIO<P>::store(orho, site, res);
+    if (a.write_z) SpinorIO<P>::store(oz, site, z);
     Spinor<float> p = z;
     if (!a.first) {
 #pragma unroll
