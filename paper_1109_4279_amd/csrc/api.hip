@@ -677,6 +677,19 @@ static int sap_cache_mode(const Batch& B, int nitems) {
 }
 
 
+// The plain FP64 solver's operator kept on the CU (registers and LDS): with 256-site blocks and
+// enough of them that reloading would stream the operator from the Infinity Cache in every MR
+// step.  Half-sweeps, reloading / on the CU: 32^3 x 64 1213 / 1028 us,
+// 24^3 x 48 386 / 374, 16^3 x 32 (256 blocks) 66.5 / 60.4, 16^4 (128) 51.9 / 50.2, but 8^3 x 16
+// (32 blocks, whose operators stay in L2) 37.8 / 42.1; smaller blocks leave part of the lanes
+// and of that gain: 2x4^3 64.0 / 71.5, 4x3^3 41.4 / 48.8.
+static int sap_cache_mode_f64(const Batch& B, int bvol, int nitems, int eo) {
+  if (eo) return 0;
+  const int forced = B.lat[0]->opt_sap_cache;
+  if (forced >= 0) return forced;
+  return bvol == 256 && 2 * nitems >= device_cus() ? 1 : 0;
+}
+
 // largest border entry count of the batch's blocks of volume bv
 static int border_entries_of(const Batch& B, int bv) {
   int n = 0;
@@ -751,7 +764,7 @@ static void run_sap_halfsweep(Batch& B, int prec, int nr, int colour, int nmr, F
     a.border = border;
     a.write_rho = wrho;
     a.write_z = wz;
-    a.cache = sap_cache_mode(B, it.n);
+    a.cache = prec == P_F64 ? sap_cache_mode_f64(B, bv, it.n, eo) : sap_cache_mode(B, it.n);
     a.uniform_bvol = bv;
     a.odd_rho = odd_rho;
     // (with the operator cached the launch has one work-group per CU, and the entries'

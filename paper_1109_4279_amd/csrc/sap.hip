@@ -23,6 +23,8 @@ __global__ __launch_bounds__(256) void k_sap_mr(SapLaunch a) {
   extern __shared__ double smem_d[];
   double* red = smem_d;                                   // SAP_MAX_WAVES * 3 * NR doubles
   cplx<R>* lds = (cplx<R>*)(smem_d + SAP_MAX_WAVES * 3 * NR);  // [NR][12][bvol]
+  // FP64 with CACHE: the links of directions 1..3 of every site, [3][9][bvol]
+  constexpr bool LINKS_LDS = CACHE && P == P_F64;
 
   for (int it0 = blockIdx.x; it0 < a.nitems; it0 += gridDim.x) {
     const WorkItem w = a.items[xcd_remap(it0, a.nitems)];
@@ -99,7 +101,14 @@ __global__ __launch_bounds__(256) void k_sap_mr(SapLaunch a) {
     // is loaded once per half-sweep and kept in registers across the MR steps (this needs
     // the whole register file of a SIMD, one wavefront each); otherwise it is reloaded
     // from the caches each step and two work-groups can share a CU.
-    SU3<R> Uf[CACHE ? 4 : 1], Ub[CACHE ? 4 : 1];
+    // In FP64 the operator of a 256-site block is 295 KB: direction 0's links and the clover
+    // blocks go to registers (216 of the 512 that one wavefront per SIMD has), the other links
+    // to LDS, where the backward hops read their neighbour's.  Reloaded each step, the block
+    // operators of an XCD's 32 CUs exceed its L2 and every step streams them from the Infinity
+    // Cache.
+    constexpr int NU = !CACHE ? 1 : LINKS_LDS ? 1 : 4;
+    SU3<R> Uf[NU], Ub[NU];
+    cplx<R>* lnk = lds + (size_t)NR * 12 * bvol;
     Herm6<R> Cl[CACHE ? 2 : 1];
     int nfw[4], nbw[4], phf[4], phb[4];
     bool inf[4], inb[4];
@@ -113,9 +122,17 @@ __global__ __launch_bounds__(256) void k_sap_mr(SapLaunch a) {
     }
     if (CACHE) {
 #pragma unroll
-      for (int mu = 0; mu < 4; ++mu) {
-        Uf[CACHE ? mu : 0] = LinkIO<P>::load(L.gauge, L.gscale, g.V, mu, s);
-        Ub[CACHE ? mu : 0] = LinkIO<P>::load(L.gauge, L.gscale, g.V, mu, inb[mu] ? nbw[mu] : s);
+      for (int mu = 0; mu < NU; ++mu) {
+        Uf[mu] = LinkIO<P>::load(L.gauge, L.gscale, g.V, mu, s);
+        Ub[mu] = LinkIO<P>::load(L.gauge, L.gscale, g.V, mu, inb[mu] ? nbw[mu] : s);
+      }
+      if (LINKS_LDS && active) {  // (read after the first step's barrier)
+#pragma unroll
+        for (int mu = 1; mu < 4; ++mu) {
+          const SU3<R> u = LinkIO<P>::load(L.gauge, L.gscale, g.V, mu, s);
+#pragma unroll
+          for (int k = 0; k < 9; ++k) lnk[((mu - 1) * 9 + k) * bvol + t] = u.m[k / 3][k % 3];
+        }
       }
 #pragma unroll
       for (int blk = 0; blk < 2; ++blk) Cl[CACHE ? blk : 0] = CloverIO<P>::load(L.clov, L.cscale, g.V, s, blk);
@@ -132,12 +149,26 @@ __global__ __launch_bounds__(256) void k_sap_mr(SapLaunch a) {
 #pragma unroll
       for (int r = 0; r < NR; ++r) zero(q[r]);
       if (active) {
+        // the link of direction MU at local site l (global index n), kept as `reg` where cached
+        auto link = [&](auto MUc, const SU3<R>* reg, int n, int l) {
+          constexpr int MU = decltype(MUc)::value;
+          if constexpr (LINKS_LDS && MU > 0) {
+            SU3<R> u;
+#pragma unroll
+            for (int k = 0; k < 9; ++k) u.m[k / 3][k % 3] = lnk[((MU - 1) * 9 + k) * bvol + l];
+            return u;
+          } else if constexpr (CACHE) {
+            return reg[MU];
+          } else {
+            return LinkIO<P>::load_raw(L.gauge, L.gscale, g.V, MU, n);
+          }
+        };
         auto hop = [&](auto MUc) {
           constexpr int MU = decltype(MUc)::value;
           if (inf[MU]) {
             const int ln = nfw[MU] - tile * bvol;
             // uncached 16-bit links are used unscaled, the scale joins the hop weight
-            SU3<R> u = CACHE ? Uf[CACHE ? MU : 0] : LinkIO<P>::load_raw(L.gauge, L.gscale, g.V, MU, s);
+            const SU3<R> u = link(MUc, Uf, s, t);
             const R w = R(-0.5) * (CACHE ? R(phf[MU]) : R(phf[MU]) * LinkIO<P>::scale(L.gscale, s));
 #pragma unroll
             for (int r = 0; r < NR; ++r) {
@@ -149,7 +180,7 @@ __global__ __launch_bounds__(256) void k_sap_mr(SapLaunch a) {
           }
           if (inb[MU]) {
             const int ln = nbw[MU] - tile * bvol;
-            SU3<R> u = CACHE ? Ub[CACHE ? MU : 0] : LinkIO<P>::load_raw(L.gauge, L.gscale, g.V, MU, nbw[MU]);
+            const SU3<R> u = link(MUc, Ub, nbw[MU], ln);
             const R w = R(-0.5) * (CACHE ? R(phb[MU]) : R(phb[MU]) * LinkIO<P>::scale(L.gscale, nbw[MU]));
 #pragma unroll
             for (int r = 0; r < NR; ++r) {
@@ -241,17 +272,21 @@ __global__ __launch_bounds__(256) void k_sap_mr(SapLaunch a) {
   }
 }
 
-size_t sap_lds_bytes(int prec, int nr, int bvol) {
+size_t sap_lds_bytes(int prec, int nr, int bvol, bool cache) {
   const size_t cb = prec == P_F64 ? 16 : 8;
-  return sizeof(double) * SAP_MAX_WAVES * 3 * nr + cb * 12 * (size_t)nr * bvol;
+  const size_t links = prec == P_F64 && cache ? cb * 27 * (size_t)bvol : 0;
+  return sizeof(double) * SAP_MAX_WAVES * 3 * nr + cb * 12 * (size_t)nr * bvol + links;
 }
 
 template <int P, bool C, int BV>
 static void launch_pcb(const SapLaunch& a, int nr, int grid, int threads, size_t lds, hipStream_t st) {
-  if (nr <= 1)
-    hipLaunchKernelGGL((k_sap_mr<P, 1, C, BV>), dim3(grid), dim3(threads), lds, st, a);
-  else
-    hipLaunchKernelGGL((k_sap_mr<P, 2, C, BV>), dim3(grid), dim3(threads), lds, st, a);
+  if constexpr (P != P_F64) {  // (FP64: one rhs per work-group only)
+    if (nr > 1) {
+      hipLaunchKernelGGL((k_sap_mr<P, 2, C, BV>), dim3(grid), dim3(threads), lds, st, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_sap_mr<P, 1, C, BV>), dim3(grid), dim3(threads), lds, st, a);
 }
 
 template <int P, bool C>
@@ -264,17 +299,15 @@ static void launch_pc(const SapLaunch& a, int nr, int grid, int threads, size_t 
 
 template <int P>
 static void launch_p(const SapLaunch& a, int nr, int grid, int threads, size_t lds, hipStream_t st) {
-  if constexpr (P != P_F64) {
-    if (a.cache) {
-      launch_pc<P, true>(a, nr, grid, threads, lds, st);
-      return;
-    }
+  if (a.cache) {
+    launch_pc<P, true>(a, nr, grid, threads, lds, st);
+    return;
   }
   launch_pc<P, false>(a, nr, grid, threads, lds, st);
 }
 
 void launch_sap_mr(int prec, int nr, const SapLaunch& a, int grid, int threads, hipStream_t st) {
-  const size_t lds = sap_lds_bytes(prec, nr, threads);
+  const size_t lds = sap_lds_bytes(prec, nr, threads, a.cache != 0);
   switch (prec) {
     case P_F64: launch_p<P_F64>(a, nr, grid, threads, lds, st); break;
     case P_F32: launch_p<P_F32>(a, nr, grid, threads, lds, st); break;

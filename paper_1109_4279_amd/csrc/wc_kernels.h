@@ -67,7 +67,7 @@ struct SapLaunch {
   int border;       // subtract the hops out of the other colour's z before solving
   int write_rho;
   int write_z;
-  int cache;        // keep links and clover in registers across the MR steps (FP32 math only)
+  int cache;        // keep the operator on the CU across the MR steps (FP64: the plain solver only)
   int uniform_bvol; // block volume shared by every lattice of the launch (0 if they differ)
   // even/odd solver, residual on odd sites (zero after every solve of the block):
   // 0 read and stored, 1 read but not stored, 2 neither read (taken as zero) nor stored
@@ -80,7 +80,7 @@ struct SapLaunch {
   int mm_xch_bytes;  // matrix-core solver: LDS bytes of its exchange slots
 };
 void launch_sap_mr(int prec, int nr, const SapLaunch& a, int grid, int block_threads, hipStream_t st);
-size_t sap_lds_bytes(int prec, int nr, int bvol);
+size_t sap_lds_bytes(int prec, int nr, int bvol, bool cache = false);
 // 16-bit storage, 4^4 blocks: block operator staged in LDS and shared by nr (1 or 2) rhs
 void launch_sap_mr_lds(int prec, int nr, const SapLaunch& a, int grid, hipStream_t st);
 
