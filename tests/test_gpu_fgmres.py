@@ -117,3 +117,21 @@ def test_fgmres_dr_argument_errors():
     assert e.value.code == -1
     with pytest.raises(wc.WCError):
         lat.solve_fgmres_dr(b, k=-1, nkv=8)
+
+
+@pytest.mark.parametrize("nkv,k", [(2, 0), (6, 3), (32, 10)])
+def test_arnoldi_cycle_lengths_on_a_ragged_lattice(nkv, k):
+    """Cycles from two columns to the longest (32 basis vectors, eight per wavefront of the
+    update) on 1728 sites, whose last 256-site chunk is ragged, two right-hand sides, a weak
+    preconditioner so that long cycles fill: iteration counts against the oracle."""
+    dims, block, m0, csw = (8, 6, 6, 6), (4, 3, 3, 3), -0.1, 1.0
+    lat = lattice(dims, block, m0, csw)
+    U, A = gauge(dims), clover(dims, m0, csw)
+    b = synth.gaussian_spinor(dims, nrhs=2, seed=62)
+    x, st = lat.solve_fgmres_dr(to_dev(b), k=k, nkv=nkv, ncy=1, nmr=1, tol=1e-10, sap_prec="f64")
+    x = to_np(x)
+    for r in range(2):
+        assert st[r]["status"] == 0
+        assert dirac.norm(b[r] - dirac.apply_D(U, A, x[r])) / dirac.norm(b[r]) <= 1e-10
+        ref = solvers.sap_fgmres_dr(U, A, b[r], block, nmr=1, ncy=1, m=nkv, k=k, tol=1e-10)
+        assert abs(st[r]["iters"] - ref.iters) <= 1
