@@ -655,7 +655,7 @@ def profile_run(wc, torch, dev):
     p = params(wc, storage, True, basis_prec=basis)
     lat.solve(pts, p)
     (_, st), ms = sync_time(torch, lambda: lat.solve(pts, p))
-    rf = roofline_record(lat, 663552, storage, 12, BLOCK, f"k_sap_eo<{storage}, 1 rhs, reloaded>, 24^3x48 x 12 rhs")
+    rf = roofline_record(lat, 663552, storage, 12, BLOCK, f"even/odd block solver on {storage} storage, 24^3x48 x 12 rhs")
     dw = dirac_rates(lat, 663552, ("f64", storage), nrhs=12, iters=20)
     print(json.dumps({"profile": "24^3x48 x 12 point sources", "storage": storage, "basis": basis, "solve_ms": ms,
                       "iters": max(s["iters"] for s in st), "half_sweep_ms": rf["launch_ms"],
@@ -820,8 +820,9 @@ def main():
     flops = sum(solve_flops(V, s["iters"], s["restarts"], NKV, NCY, NMR, block, True) for s in st)
     etile = tuning["tiles"][storage][3]
     roofline = roofline_record(lat, V, storage, 12, block,
-                               f"k_sap_eo<{storage}, {etile} rhs per work-group, operator reloaded>: one colour "
-                               f"of 24^3x48 x 12 rhs, {NMR} steps", tile=etile)
+                               f"even/odd block solver on {storage} storage (k_sap_eo_mm on the matrix cores "
+                               f"where the library picks it, else k_sap_eo): one colour of 24^3x48 x 12 rhs, "
+                               f"{NMR} steps", tile=etile)
     pcode = {"f32": 1, "f16": 2, "bf16": 3}[storage]
     roofline["traffic"] = measured_traffic(f"k_sap_eo<{pcode}, {etile}, false>", "traffic_24c48.json")
     roofline["valu_occupancy"] = measured_valu(f"k_sap_eo<{pcode}, {etile}, false>", "valu_24c48.json")
