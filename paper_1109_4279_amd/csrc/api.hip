@@ -151,9 +151,11 @@ struct DevBuf {
     p = nullptr;
     n = 0;
   }
-  // Gives the memory to the pool.  The caller has waited for all work that uses it.
+  // Gives the memory to the pool.  The caller has waited for all work on the current device
+  // that uses it; memory of another device goes back to the runtime.
   void recycle() {
-    if (p && dev_pool().give(dev, p, n)) p = nullptr;
+    int cur = -1;
+    if (p && hipGetDevice(&cur) == hipSuccess && cur == dev && dev_pool().give(dev, p, n)) p = nullptr;
     release();
   }
   void ensure(size_t bytes) {
