@@ -276,6 +276,12 @@ int wc_force(wc_ctx* ctx, void* F, const void* phi, const wc_solver_params* p, w
  * several rhs on the matrix cores, was the fastest; the context then keeps that choice). */
 int wc_autotune(wc_ctx* ctx, int nrhs, int prec, int nr_out[4], void* stream);
 
+/* The rhs per work-group that the even/odd block solver takes on each lattice's blocks in a
+ * call on these nlat lattices and rhs counts (one lattice: nlat 1) with storage prec and the
+ * tiles and options in force: 1 or 2 the vector kernel, 4 the kernel that takes up to four
+ * rhs on the matrix cores (16-bit storage).  Touches no device.  Errors: WC_ERR_ARG. */
+int wc_sap_eo_tiles(wc_ctx* const* ctxs, int nlat, const int* nrhs, int prec, int* tiles);
+
 /* Choose the Schwarz block shape of the context among the valid shapes with at most 256
  * sites by timing a short solve (tolerance p->tol) of one Gaussian source for each;
  * re-lays the context out for the fastest.  block_out receives it. */

@@ -12,7 +12,8 @@ import ctypes
 from . import _lib
 from ._lib import PREC, REGION, SolverParams, SolverStats, WCError  # noqa: F401
 
-__all__ = ["Lattice", "SolverParams", "SolverStats", "WCError", "default_params", "solve_batch", "PREC"]
+__all__ = ["Lattice", "SolverParams", "SolverStats", "WCError", "default_params", "sap_eo_tiles", "solve_batch",
+           "PREC"]
 
 
 def _torch():
@@ -298,6 +299,19 @@ class Lattice:
         _lib.check(_lib.load().wc_bench_sap(self._ctx, PREC[prec], int(nrhs), int(nmr), int(bool(eo)), int(iters),
                                             ctypes.byref(ms), _stream(stream)))
         return ms.value
+
+
+def sap_eo_tiles(lattices, nrhs, prec):
+    """Right-hand sides per work-group of the even/odd block solver on each lattice's blocks in
+    a call on these lattices with nrhs[i] right-hand sides and storage prec: 1 or 2 the vector
+    kernel, 4 the one that takes up to four on the matrix cores."""
+    n = len(lattices)
+    if len(nrhs) != n:
+        raise WCError(-1, f"{len(nrhs)} rhs counts for {n} lattices")
+    ctxs = (ctypes.c_void_p * n)(*[lat._ctx.value for lat in lattices])
+    out = (ctypes.c_int * n)()
+    _lib.check(_lib.load().wc_sap_eo_tiles(ctxs, n, (ctypes.c_int * n)(*[int(v) for v in nrhs]), PREC[prec], out))
+    return [int(v) for v in out]
 
 
 def solve_batch(lattices, bs, params: SolverParams | None = None, stream=None, check=True, k=None, **kw):

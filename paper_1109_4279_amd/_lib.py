@@ -77,6 +77,7 @@ _SIGS = {
     "wc_link_grad": (_I, [_P, _P, _P, _P, _I, _D, _P]),
     "wc_force": (_I, [_P, _P, _P, ctypes.POINTER(SolverParams), ctypes.POINTER(SolverStats), _P, _P, _P]),
     "wc_autotune": (_I, [_P, _I, _I, ctypes.POINTER(_I), _P]),
+    "wc_sap_eo_tiles": (_I, [ctypes.POINTER(_P), _I, ctypes.POINTER(_I), _I, ctypes.POINTER(_I)]),
     "wc_set_option": (_I, [_P, _I, _I]),
     "wc_set_tiles": (_I, [_P, _I, _I, _I, _I]),
     "wc_pseudofermion_action": (_I, [_P, _P, ctypes.POINTER(SolverParams), ctypes.POINTER(_D), _P, _P,

@@ -692,15 +692,15 @@ static int sap_cache_mode_f64(const Batch& B, int bvol, int nitems, int eo) {
   return bvol == 256 && 2 * nitems >= device_cus() ? 1 : 0;
 }
 
-// largest border entry count of the batch's blocks of volume bv
-static int border_entries_of(const Batch& B, int bv) {
+// largest border entry count of the lattices' blocks of volume bv
+static int border_entries_of(const std::vector<wc_ctx*>& lat, int bv) {
   int n = 0;
-  for (auto* c : B.lat)
+  for (auto* c : lat)
     if (c->g.bvol == bv) n = std::max(n, border_entry_count(c->g.B));
   return n;
 }
 
-// The rhs tile of the block solver on the blocks of volume bv: nr, or, where the choice is
+// The rhs tile of the block solver on the blocks of volume bv of a call on lat with nrhs: nr, or, where the choice is
 // left (SAP_MM_RHS), the matrix-core kernel or one rhs per work-group of the vector one.
 //
 // One work item of the matrix-core kernel takes the same time for one to four rhs, and with
@@ -714,15 +714,15 @@ static int border_entries_of(const Batch& B, int bv) {
 // 128 sites leave room for two work-groups and more on a CU and lanes of the vector kernel
 // idle: 4x3^3 98 / 67 (256 blocks, 8 rhs; 4 rhs 53 / 56); 2x4^3 159 / 68 (512 blocks, 4 rhs);
 // 2^4 550 / 111 (4096 blocks, 4 rhs).
-static int sap_tile(const Batch& B, int nr, int bv) {
+static int sap_tile(const std::vector<wc_ctx*>& lat, const std::vector<int>& nrhs, int nr, int bv) {
   if (nr != SAP_MM_RHS) return nr;
-  if (sap_eo_mm_lds_bytes(bv, border_entries_of(B, bv)) > LDS_MAX_BYTES) return 1;
+  if (sap_eo_mm_lds_bytes(bv, border_entries_of(lat, bv)) > LDS_MAX_BYTES) return 1;
   long long vec = 0, mat = 0;
-  for (size_t i = 0; i < B.lat.size(); ++i) {
-    if (B.lat[i]->g.bvol != bv) continue;
-    const long long blocks = B.lat[i]->g.ntiles / 2;
-    vec += blocks * B.nrhs[i];
-    mat += blocks * ((B.nrhs[i] + SAP_MM_RHS - 1) / SAP_MM_RHS);
+  for (size_t i = 0; i < lat.size(); ++i) {
+    if (lat[i]->g.bvol != bv) continue;
+    const long long blocks = lat[i]->g.ntiles / 2;
+    vec += blocks * nrhs[i];
+    mat += blocks * ((nrhs[i] + SAP_MM_RHS - 1) / SAP_MM_RHS);
   }
   const long long cus = device_cus();
   const bool faster = bv <= 128 ? vec > 4 * cus : vec > 2 * cus && 2.7 * ((mat + cus - 1) / cus) * cus < vec;
@@ -743,9 +743,9 @@ static void run_sap_halfsweep(Batch& B, int prec, int nr, int colour, int nmr, F
   for (int bv : B.bvols()) {
     // the even/odd solver's border update runs from LDS entries when they fit a
     // work-group's LDS next to the exchange rows (else per site)
-    const int tile = sap_tile(B, nr, bv);
+    const int tile = sap_tile(B.lat, B.nrhs, nr, bv);
     const bool mm = tile == SAP_MM_RHS;
-    int bentries = border_entries_of(B, bv);
+    int bentries = border_entries_of(B.lat, bv);
     if (eo && !mm && sap_eo_lds_bytes(prec, tile, bv, bentries) > LDS_MAX_BYTES) bentries = 0;
     const ItemList& it = B.items_sap(colour, tile, bv);
     if (it.n == 0) continue;
@@ -956,7 +956,7 @@ static void prepare_solver(Batch& B, const SolveSetup& s, bool fgcr = true) {
   for (int nr : {1, s.nr_d, s.nr_d32})
     for (int sel = 0; sel < 3; ++sel) B.items_dirac(nr, sel);
   for (int bv : B.bvols())
-    for (int c = 0; c < 2; ++c) B.items_sap(c, sap_tile(B, s.nr_s, bv), bv);
+    for (int c = 0; c < 2; ++c) B.items_sap(c, sap_tile(B.lat, B.nrhs, s.nr_s, bv), bv);
   HIPCK(hipDeviceSynchronize());
 }
 
@@ -2245,6 +2245,22 @@ int wc_autotune(wc_ctx* c, int nrhs, int prec, int nr_out[4], void* stream) {
       nr_out[2] = ns;
       nr_out[3] = std::max(ne, 1);
     }
+  });
+}
+
+int wc_sap_eo_tiles(wc_ctx* const* ctxs, int nlat, const int* nrhs, int prec, int* tiles) {
+  return guarded([&] {
+    require(ctxs && nlat >= 1 && nrhs && tiles, WC_ERR_ARG, "null argument or nlat < 1");
+    check_prec(prec);
+    const std::vector<wc_ctx*> cs(ctxs, ctxs + nlat);
+    const std::vector<int> ns(nrhs, nrhs + nlat);
+    int max_nrhs = 0;
+    for (int i = 0; i < nlat; ++i) {
+      require(cs[i] && ns[i] >= 1, WC_ERR_ARG, "bad lattice argument");
+      max_nrhs = std::max(max_nrhs, ns[i]);
+    }
+    const int nr = pick_nr(cs[0], max_nrhs, prec, true, 0, 1);
+    for (int i = 0; i < nlat; ++i) tiles[i] = sap_tile(cs, ns, nr, cs[i]->g.bvol);
   });
 }
 
