@@ -593,7 +593,7 @@ void launch_clover_mm(int V, const void* clov_eo16, void* dst, hipStream_t st) {
                      (uint32_t*)dst);
 }
 
-static int mm_waves(int bvol) { return ((bvol + 1) / 2 + 15) / 16; }
+int sap_eo_mm_waves(int bvol) { return ((bvol + 1) / 2 + 15) / 16; }
 
 size_t sap_eo_mm_xch_bytes(int bvol, int border_entries) {
   const size_t slots = (size_t)(2 * ((bvol + 1) / 2) + 1) * MM_SLOT;
@@ -608,7 +608,7 @@ size_t sap_eo_mm_lds_bytes(int bvol, int border_entries) {
 
 void launch_sap_eo_mm(int prec, const SapLaunch& a, int bvol, int border_entries, hipStream_t st) {
   const size_t lds = sap_eo_mm_lds_bytes(bvol, border_entries);
-  const int threads = 64 * mm_waves(bvol);
+  const int threads = 64 * sap_eo_mm_waves(bvol);
   if (prec == P_F16)
     hipLaunchKernelGGL((k_sap_eo_mm<P_F16>), dim3(a.nitems), dim3(threads), lds, st, a);
   else

@@ -94,6 +94,8 @@ size_t sap_eo_lds_bytes(int prec, int nr, int max_bvol, int border_entries);
 constexpr int SAP_MM_RHS = 4;
 size_t sap_eo_mm_xch_bytes(int bvol, int border_entries);
 size_t sap_eo_mm_lds_bytes(int bvol, int border_entries);
+constexpr int SAP_MM_CU_WAVES = 8;  // its wavefronts on a CU (256 registers each)
+int sap_eo_mm_waves(int bvol);      // and in a work-group
 // its clover operand from the 16-bit even/odd clover field: SAP_MM_CLOVER_BYTES per site
 constexpr size_t SAP_MM_CLOVER_BYTES = 8 * 9 * 4;
 void launch_clover_mm(int V, const void* clov_eo16, void* dst, hipStream_t st);
