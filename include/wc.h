@@ -293,8 +293,16 @@ int wc_autotune_block(wc_ctx* ctx, const wc_solver_params* p, int block_out[4], 
 int wc_bench_dirac(wc_ctx* ctx, int prec, int nrhs, int region, int iters, double* ms, void* stream);
 int wc_bench_sap(wc_ctx* ctx, int prec, int nrhs, int nmr, int eo, int iters, double* ms, void* stream);
 
-/* Release everything the context owns. */
+/* Release everything the context owns.  Waits for the work on its GPU that is enqueued.  Device
+ * memory of destroyed contexts (and of finished wc_link_grad, wc_force and
+ * wc_pseudofermion_action calls) stays with the library for the next contexts and calls, up
+ * to 2 GiB per GPU, of which the memory kept longest is freed first. */
 void wc_destroy(wc_ctx* ctx);
+
+/* Give the memory kept so on the current GPU back to the runtime, for a program that needs it
+ * elsewhere (another allocator's requests do not reach it; the library's own empty it before
+ * they fail).  *bytes (may be NULL) receives how much that was. */
+int wc_empty_pool(long long* bytes);
 
 /* Message of the last error on this thread (static storage, valid until the next call). */
 const char* wc_last_error(void);

@@ -12,8 +12,8 @@ import ctypes
 from . import _lib
 from ._lib import PREC, REGION, SolverParams, SolverStats, WCError  # noqa: F401
 
-__all__ = ["Lattice", "SolverParams", "SolverStats", "WCError", "default_params", "sap_eo_tiles", "solve_batch",
-           "PREC"]
+__all__ = ["Lattice", "SolverParams", "SolverStats", "WCError", "default_params", "empty_pool", "sap_eo_tiles",
+           "solve_batch", "PREC"]
 
 
 def _torch():
@@ -299,6 +299,14 @@ class Lattice:
         _lib.check(_lib.load().wc_bench_sap(self._ctx, PREC[prec], int(nrhs), int(nmr), int(bool(eo)), int(iters),
                                             ctypes.byref(ms), _stream(stream)))
         return ms.value
+
+
+def empty_pool():
+    """Give the device memory that the library keeps of destroyed lattices (up to 2 GiB on the
+    current GPU) back to the runtime, for torch or others to allocate; returns its bytes."""
+    n = ctypes.c_longlong()
+    _lib.check(_lib.load().wc_empty_pool(ctypes.byref(n)))
+    return int(n.value)
 
 
 def sap_eo_tiles(lattices, nrhs, prec):

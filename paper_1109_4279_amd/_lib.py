@@ -87,6 +87,7 @@ _SIGS = {
     "wc_bench_dirac": (_I, [_P, _I, _I, _I, _I, ctypes.POINTER(_D), _P]),
     "wc_bench_sap": (_I, [_P, _I, _I, _I, _I, _I, ctypes.POINTER(_D), _P]),
     "wc_destroy": (None, [_P]),
+    "wc_empty_pool": (_I, [ctypes.POINTER(ctypes.c_longlong)]),
     "wc_last_error": (ctypes.c_char_p, []),
     "wc_version": (_I, []),
 }

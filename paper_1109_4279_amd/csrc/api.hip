@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "wc.h"
+#include "block_pool.h"
 #include "dense_host.h"
 #include "wc_kernels.h"
 
@@ -85,48 +86,48 @@ static hipGraphExec_t capture_graph(hipStream_t cap, const std::function<void(hi
 // dirac_apply and its gradients: 1.39 ms a call with them, 0.45 ms of kernels).  A block enters
 // the pool only when no work on any stream can still use it (its giver has waited for that),
 // so whoever takes it next, on any stream or thread, may write it at once.  At most POOL_BYTES
-// per device are kept, the rest goes back to the runtime; an allocation that fails empties the
-// device's pool and is tried again.
+// per device are kept; the blocks kept longest go back to the runtime for new ones, all of a
+// device's on wc_empty_pool and when an allocation fails, which is then tried again.
 constexpr size_t POOL_BYTES = size_t(2) << 30;
 
 struct DevPool {
-  struct Dev {
-    std::multimap<size_t, void*> blocks;
-    size_t bytes = 0;
-  };
   std::mutex mu;
-  std::map<int, Dev> devs;
+  std::map<int, BlockPool> devs;
 
-  // a kept block of at least `bytes` and at most a quarter more, or null
+  BlockPool& of(int dev) { return devs.try_emplace(dev, POOL_BYTES).first->second; }
+
   void* take(int dev, size_t bytes, size_t* got) {
     std::lock_guard<std::mutex> lock(mu);
-    Dev& d = devs[dev];
-    auto it = d.blocks.lower_bound(bytes);
-    if (it == d.blocks.end() || it->first > bytes + bytes / 4 + 4096) return nullptr;
-    void* p = it->second;
-    *got = it->first;
-    d.bytes -= it->first;
-    d.blocks.erase(it);
-    return p;
+    return of(dev).take(bytes, got);
   }
-  // false: the pool is full, the caller frees the block
-  bool give(int dev, void* p, size_t bytes) {
-    std::lock_guard<std::mutex> lock(mu);
-    Dev& d = devs[dev];
-    if (d.bytes + bytes > POOL_BYTES) return false;
-    d.blocks.emplace(bytes, p);
-    d.bytes += bytes;
-    return true;
-  }
-  void empty(int dev) {
-    std::multimap<size_t, void*> blocks;
-    {
-      std::lock_guard<std::mutex> lock(mu);
-      Dev& d = devs[dev];
-      blocks.swap(d.blocks);
-      d.bytes = 0;
+  // false: not kept, the caller frees the block
+  bool give(int dev, void* p, size_t bytes) noexcept {
+    try {
+      for (;;) {
+        void* old = nullptr;
+        {
+          std::lock_guard<std::mutex> lock(mu);
+          BlockPool& b = of(dev);
+          if (b.fits(bytes)) return b.give(p, bytes);
+          if (bytes > b.limit() || !(old = b.oldest(nullptr))) return false;
+        }
+        (void)hipFree(old);
+      }
+    } catch (...) {
+      return false;
     }
-    for (auto& kv : blocks) (void)hipFree(kv.second);
+  }
+  // bytes given back
+  size_t empty(int dev) {
+    for (size_t sum = 0, n = 0;; sum += n) {
+      void* p;
+      {
+        std::lock_guard<std::mutex> lock(mu);
+        p = of(dev).oldest(&n);
+      }
+      if (!p) return sum;
+      (void)hipFree(p);
+    }
   }
 };
 
@@ -2327,6 +2328,15 @@ int wc_autotune_block(wc_ctx* c, const wc_solver_params* p, int block_out[4], vo
     layout(c, best_b.data(), st);
     if (block_out)
       for (int m = 0; m < 4; ++m) block_out[m] = best_b[m];
+  });
+}
+
+int wc_empty_pool(long long* bytes) {
+  return guarded([&] {
+    int dev = -1;
+    HIPCK(hipGetDevice(&dev));
+    const size_t n = dev_pool().empty(dev);
+    if (bytes) *bytes = (long long)n;
   });
 }
 
