@@ -1583,15 +1583,16 @@ wc_ctx::~wc_ctx() {
   batches.clear();
   wc::drop_multi_batches(this);
   if (cap) (void)hipStreamDestroy(cap);
-  // Once nothing on the device can still use them, the context's own buffers go to the pool
-  // (if the wait fails, hipFree waits for them one by one).
+  // Once nothing on the device can still use them, the context's own buffers go to the pool.  The
+  // wait is that of hipFree, on the smallest of them: hipDeviceSynchronize would invalidate a
+  // capture that another thread has under way.  (If it fails the buffers are freed one by one.)
   int cur = -1;
-  if (hipGetDevice(&cur) != hipSuccess || cur != dev || hipDeviceSynchronize() != hipSuccess) {
+  if (hipGetDevice(&cur) != hipSuccess || cur != dev || !tables.p || hipFree(tables.p) != hipSuccess) {
     (void)hipGetLastError();
     return;
   }
+  tables.p = nullptr;
   Ucanon.recycle();
-  tables.recycle();
   for (int p = 0; p < 4; ++p)
     for (wc::DevBuf* b : {&links[p], &lscale[p], &clov[p], &cscale[p], &clov_eo[p], &cscale_eo[p], &clov_mm[p]})
       b->recycle();
