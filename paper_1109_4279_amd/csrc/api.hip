@@ -291,7 +291,9 @@ struct wc_ctx {
   bool have_clov[4] = {false, false, false, false};
   wc::DevBuf clov_eo[4], cscale_eo[4];  // even/odd block solver: A on even, A^-1 on odd sites
   bool have_clov_eo[4] = {false, false, false, false};
-  wc::DevBuf clov_mm[4];  // the matrix-core block solver's clover rows (16-bit storage only)
+  // the matrix-core block solver's clover rows (16-bit storage, made for the first call it takes)
+  wc::DevBuf clov_mm[4];
+  bool have_clov_mm[4] = {false, false, false, false};
   // layout tables, one allocation and one copy: tile lists of the two colours, and the block
   // solvers' (LatDesc)
   wc::DevBuf tables;
@@ -346,14 +348,20 @@ static void ensure_clover_eo(wc_ctx* c, int prec, hipStream_t st) {
     if (is16(prec)) c->cscale_eo[prec].ensure(sizeof(float) * 2 * c->g.V);
     launch_clover_convert(prec, c->g, c->clov_eo[P_F64].p, c->clov_eo[prec].p, c->cscale_eo[prec].as<float>(), st);
     HIPCK(hipGetLastError());
-    if (is16(prec)) {
-      c->clov_mm[prec].ensure((size_t)c->g.V * SAP_MM_CLOVER_BYTES);
-      launch_clover_mm(c->g.V, c->clov_eo[prec].p, c->clov_mm[prec].p, st);
-      HIPCK(hipGetLastError());
-    }
     c->have_clov_eo[prec] = true;
   }
 }
+
+static void ensure_clover_mm(wc_ctx* c, int prec, hipStream_t st) {
+  ensure_clover_eo(c, prec, st);
+  if (c->have_clov_mm[prec]) return;
+  c->clov_mm[prec].ensure((size_t)c->g.V * SAP_MM_CLOVER_BYTES);
+  launch_clover_mm(c->g.V, c->clov_eo[prec].p, c->clov_mm[prec].p, st);
+  HIPCK(hipGetLastError());
+  c->have_clov_mm[prec] = true;
+}
+
+static int sap_tile(const std::vector<wc_ctx*>& lat, const std::vector<int>& nrhs, int nr, int bv);
 
 // ---------------------------------------------------------------------------- batches
 
@@ -438,11 +446,29 @@ struct Batch {
     partials.ensure(sizeof(double) * (size_t)total_chunks * pw);
   }
 
-  const LatDesc* lats(int prec, hipStream_t st, bool eo = false) {
+  // the lattices whose blocks the even/odd solver of rhs tile nr solves on the matrix cores
+  std::vector<bool> on_matrix_cores(int nr) const {
+    std::vector<bool> v(lat.size(), false);
+    if (nr != SAP_MM_RHS) return v;
+    for (int bv : bvols()) {
+      const bool mm = sap_tile(lat, nrhs, nr, bv) == SAP_MM_RHS;
+      for (size_t i = 0; i < lat.size(); ++i)
+        if (lat[i]->g.bvol == bv) v[i] = mm;
+    }
+    return v;
+  }
+
+  // descriptors with the operator in prec; eo: and what the even/odd block solver of rhs tile
+  // nr_sap reads
+  const LatDesc* lats(int prec, hipStream_t st, bool eo = false, int nr_sap = 0) {
     bool stale = !have_lats[prec] || (eo && !lats_eo[prec]);
     for (auto* c : lat) stale |= !c->have_links[prec] || !c->have_clov[prec];
+    const std::vector<bool> mm = on_matrix_cores(eo ? nr_sap : 0);
+    for (size_t i = 0; i < lat.size() && !stale; ++i)
+      stale = mm[i] && !(lat[i]->have_clov_mm[prec] && h_lats[prec][i].clov_mm);
     if (!stale) return d_lats[prec].as<LatDesc>();
     eo = eo || lats_eo[prec];
+    have_lats[prec] = false;
     h_lats[prec].clear();
     long long foff = 0;
     int sys0 = 0, part0 = 0;
@@ -475,7 +501,8 @@ struct Batch {
         ensure_clover_eo(c, prec, st);
         L.clov_eo = c->clov_eo[prec].p;
         L.cscale_eo = c->cscale_eo[prec].as<float>();
-        L.clov_mm = c->clov_mm[prec].p;
+        if (mm[i]) ensure_clover_mm(c, prec, st);
+        if (c->have_clov_mm[prec]) L.clov_mm = c->clov_mm[prec].p;
       }
       h_lats[prec].push_back(L);
       foff += (long long)nrhs[i] * c->g.V;
@@ -752,7 +779,7 @@ static void run_sap_halfsweep(Batch& B, int prec, int nr, int colour, int nmr, F
   require(mm_asked || (nr >= 1 && nr <= (prec == P_F64 ? 1 : 2)), WC_ERR_ARG, "block-solver rhs tile out of range");
   require(mm_asked || (eo ? sap_eo_lds_bytes(prec, nr, B.max_bvol, 0) : sap_lds_bytes(prec, nr, B.sap_threads())) <= 65536,
           WC_ERR_GEOMETRY, "block too large for LDS");
-  const LatDesc* L = B.lats(prec, st, eo != 0);
+  const LatDesc* L = B.lats(prec, st, eo != 0, nr);
   // one launch per block volume of the batch, each with work-groups sized for its own
   // blocks (one launch sized for the largest would leave the lanes of smaller blocks idle)
   for (int bv : B.bvols()) {
@@ -966,7 +993,7 @@ static void prepare_solver(Batch& B, const SolveSetup& s, bool fgcr = true) {
   B.hist.ensure(sizeof(double) * HIST_MAX * B.nsys);
   // everything a captured cycle touches must exist before capture starts
   B.lats(P_F64, nullptr);
-  B.lats(s.sap_prec, nullptr, s.eo != 0);
+  B.lats(s.sap_prec, nullptr, s.eo != 0, s.nr_s);
   if (fgcr && s.basis_prec != P_F64) B.lats(P_F32, nullptr);
   for (int nr : {1, s.nr_d, s.nr_d32})
     for (int sel = 0; sel < 3; ++sel) B.items_dirac(nr, sel);
@@ -1567,6 +1594,7 @@ static void layout(wc_ctx* c, const int* block, hipStream_t st) {
     c->have_links[p] = false;
     c->have_clov[p] = false;
     c->have_clov_eo[p] = false;
+    c->have_clov_mm[p] = false;
   }
   ensure_links(c, P_F64, st);
   if (c->have_clover) {
@@ -1682,6 +1710,7 @@ int wc_create_clover(wc_ctx* c, double m0, double csw, void* stream) {
     for (int p = 0; p < 4; ++p) {
       c->have_clov[p] = (p == P_F64);
       c->have_clov_eo[p] = false;
+      c->have_clov_mm[p] = false;
     }
     for (auto& kv : c->batches)
       for (int p = 0; p < 4; ++p) kv.second->have_lats[p] = false;
@@ -2185,7 +2214,7 @@ int wc_bench_sap(wc_ctx* c, int prec, int nrhs, int nmr, int eo, int iters, doub
       HIPCK(hipMemsetAsync(B.sap_z.scale(), 0, sizeof(float) * B.sites_rhs, st));
     }
     const int nr = pick_nr(c, nrhs, prec, true, 0, eo);
-    B.lats(prec, st, eo != 0);
+    B.lats(prec, st, eo != 0, nr);
     HIPCK(hipStreamSynchronize(st));
     int colour = 0;
     *ms = time_launches(c, st, iters, [&](hipStream_t s) {
