@@ -126,6 +126,7 @@ void wc_default_params(wc_solver_params* p);
  *                     registers when a launch has at most two work items per CU (the plain
  *                     FP64 one in registers and LDS, by its own rule);
  *                     0 reload it in every phase; 1 keep it (not the even/odd FP64 solver).
+ *                     0 and 1 also choose the vector kernel over the matrix-core one.
  * WC_OPT_DIRAC_STAGE  -1 automatic (default) and 1: D_w stages each 256-site tile's input
  *                     in LDS (lattices with 256-site blocks, tiles that fit); 0 never.
  * Both select kernels only; results agree to rounding.  Errors: WC_ERR_ARG. */

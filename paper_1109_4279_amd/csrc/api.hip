@@ -753,6 +753,7 @@ static int border_entries_of(const std::vector<wc_ctx*>& lat, int bv) {
 // behind the vector kernel.
 static int sap_tile(const std::vector<wc_ctx*>& lat, const std::vector<int>& nrhs, int nr, int bv) {
   if (nr != SAP_MM_RHS) return nr;
+  if (lat[0]->opt_sap_cache >= 0) return 1;  // (asked for the vector kernel, one way or the other)
   const int entries = border_entries_of(lat, bv);
   const size_t mm_lds = sap_eo_mm_lds_bytes(bv, entries);
   if (mm_lds > LDS_MAX_BYTES) return 1;
