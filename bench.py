@@ -332,8 +332,9 @@ def dirac_rates(lat, V, precs, nrhs=1, iters=50):
             if copy:
                 rec["frac_copy"] = gbs / copy
         else:
-            # the operator counted once per rhs tile of the kernel, and once for all nrhs
-            tile = lat_tile(lat, prec)
+            # the operator counted once per rhs tile of the kernel, and once for all nrhs (in FP64
+            # the kernel on the caller's arrays, one rhs per lane)
+            tile = 1 if prec == "f64" else lat_tile(lat, prec)
             g_tile = dw_bytes(prec, tile) * V * nrhs / (ms * 1e-3) / 1e9
             g_all = dw_bytes(prec, nrhs) * V * nrhs / (ms * 1e-3) / 1e9
             rec.update({"rhs_per_lane": tile, "GB/s": g_tile, "frac_hbm": g_tile / HBM_PEAK_GBS,
@@ -365,7 +366,6 @@ def tune_c4(wc, torch, lat, pts):
     best = min(times, key=times.get)
     tiles[best] = lat.autotune(12, prec=best)  # the chosen storage's tiles stay in the context
     _TILES[(id(lat), best)] = tiles[best][0]
-    _TILES[(id(lat), "f64")] = tiles[best][1]
     basis_ms = {}
     for qp in ("f64", "f32"):
         _, _, basis_ms[qp] = timed_solve(lat, pts, params(wc, best, True, basis_prec=qp), torch)
@@ -651,7 +651,6 @@ def profile_run(wc, torch, dev):
     basis = os.environ.get("WC_BENCH_BASIS", "f32")
     tiles = lat.autotune(12, prec=storage)
     _TILES[(id(lat), storage)] = tiles[0]
-    _TILES[(id(lat), "f64")] = tiles[1]
     p = params(wc, storage, True, basis_prec=basis)
     lat.solve(pts, p)
     (_, st), ms = sync_time(torch, lambda: lat.solve(pts, p))

@@ -129,14 +129,16 @@ void wc_default_params(wc_solver_params* p);
  *                     0 and 1 also choose the vector kernel over the matrix-core one.
  * WC_OPT_DIRAC_STAGE  -1 automatic (default) and 1: D_w stages each 256-site tile's input
  *                     in LDS (lattices with 256-site blocks, tiles that fit); 0 never.
+ *                     wc_apply_D in FP64 runs a kernel of its own on the caller's arrays
+ *                     (which stages by 256 sites, whatever the blocks) while this option is
+ *                     -1 and no FP64 tile nr_dirac is set, else the solvers' on packed fields.
  * Both select kernels only; results agree to rounding.  Errors: WC_ERR_ARG. */
 typedef enum { WC_OPT_SAP_CACHE = 0, WC_OPT_DIRAC_STAGE = 1 } wc_option;
 int wc_set_option(wc_ctx* ctx, int option, int value);
 
 /* Right-hand sides handled together, per storage precision prec: nr_dirac per lane of D
  * (1..4), nr_sap per work-group of the plain block solver and nr_sap_eo of the even/odd one
- * (1..2; FP64 1).  0 leaves the library's choice (or the autotuner's).  wc_apply_D in FP64 runs
- * one rhs per lane whatever the tile (the solvers' FP64 D follows it).  Errors: WC_ERR_ARG. */
+ * (1..2; FP64 1).  0 leaves the library's choice (or the autotuner's).  Errors: WC_ERR_ARG. */
 int wc_set_tiles(wc_ctx* ctx, int prec, int nr_dirac, int nr_sap, int nr_sap_eo);
 
 /* Create a context for one lattice: copies the gauge field U (device, complex128, see
@@ -160,7 +162,8 @@ int wc_clover_export(wc_ctx* ctx, void* A, void* stream);
  * D_Lambda in (WC_BLOCKS: hops between different blocks dropped, Sec. 4).  dagger = 1
  * applies D^dag = g5 D g5.  prec selects storage/arithmetic; inputs and outputs are
  * complex128 in any case (converted on the device; in FP64 the kernel works on them directly
- * and nothing is allocated).  in and out must not overlap. */
+ * and nothing is allocated, unless WC_OPT_DIRAC_STAGE or an FP64 tile asks for the packed one).
+ * in and out must not overlap. */
 int wc_apply_D(wc_ctx* ctx, void* out, const void* in, int nrhs, int prec, int region, int dagger, void* stream);
 
 /* One Schwarz half-sweep (Sec. 4): nmr MR steps from a zero start on every block of the
@@ -242,8 +245,8 @@ int wc_spinor_scale(wc_ctx* ctx, void* out, const void* in, int nrhs, double coe
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Arguments,
  * layouts and results are those of wc_apply_D (same kernels, bit-identical output).  The
  * packed input and output fields and the kernels' work list live in a fixed scratch array
- * of 128 MiB per GPU that the library holds until the process ends (FP64 does not touch it,
- * under the same limit); a call needs
+ * of 128 MiB per GPU that the library holds until the process ends (FP64 touches it only where
+ * WC_OPT_DIRAC_STAGE or a tile asks for the packed kernel, but has the same limit); a call needs
  * 256 B + 16 B per 256-site chunk and rhs tile + 2 x nrhs x V x (192 B FP64, 96 B FP32,
  * 52 B 16-bit), e.g. 16^3 x 32 in FP64 up to 2 right-hand sides.  Larger requests return
  * WC_ERR_ARG.  The operator must already be resident in prec (the FP64 one always is; any
@@ -288,8 +291,8 @@ int wc_sap_eo_tiles(wc_ctx* const* ctxs, int nlat, const int* nrhs, int prec, in
  * re-lays the context out for the fastest.  block_out receives it. */
 int wc_autotune_block(wc_ctx* ctx, const wc_solver_params* p, int block_out[4], void* stream);
 
-/* Timing helpers for the benchmark: run the D kernel (or one Schwarz half-sweep) iters
- * times back to back on internal fields between two HIP events on `stream`; *ms gets the
+/* Timing helpers for the benchmark: run the D kernel of wc_apply_D without the conversion of
+ * its arrays (or one Schwarz half-sweep) iters times back to back on internal fields between two HIP events on `stream`; *ms gets the
  * mean time per launch.  Synchronises `stream`. */
 int wc_bench_dirac(wc_ctx* ctx, int prec, int nrhs, int region, int iters, double* ms, void* stream);
 int wc_bench_sap(wc_ctx* ctx, int prec, int nrhs, int nmr, int eo, int iters, double* ms, void* stream);

@@ -304,6 +304,7 @@ struct wc_ctx {
   const uint32_t* eo_bent = nullptr;
   const uint16_t* eo_bgat = nullptr;
   int nr_dirac[4] = {0, 0, 0, 0};
+  bool f64_tile_set = false;  // nr_dirac[P_F64] is the caller's, not the autotuner's
   int nr_sap[4] = {0, 0, 0, 0};
   int nr_sap_eo[4] = {0, 0, 0, 0};
   int opt_sap_cache = -1;    // WC_OPT_SAP_CACHE: -1 automatic, 0 reload, 1 registers
@@ -1673,6 +1674,7 @@ int wc_set_tiles(wc_ctx* c, int prec, int nr_dirac, int nr_sap, int nr_sap_eo) {
     require(nr_sap >= 0 && nr_sap <= smax && nr_sap_eo >= 0 && nr_sap_eo <= smax, WC_ERR_ARG,
             "block-solver tiles must be in 0..2 (0..1 for FP64)");
     c->nr_dirac[prec] = nr_dirac;
+    if (prec == P_F64) c->f64_tile_set = nr_dirac > 0;
     c->nr_sap[prec] = nr_sap;
     c->nr_sap_eo[prec] = nr_sap_eo;
   });
@@ -1739,6 +1741,12 @@ int wc_clover_export(wc_ctx* c, void* A, void* stream) {
   });
 }
 
+// Whether an application of D_w in prec goes straight between the caller's arrays: FP64, unless
+// the caller has set a tile or the staging option, which are those of the kernel on packed fields.
+static bool apply_on_canon(const wc_ctx* c, int prec) {
+  return prec == P_F64 && !c->f64_tile_set && c->opt_dirac_stage < 0;
+}
+
 // FP64 D_w straight between the caller's arrays (no packed fields, nothing allocated)
 static void apply_D_canon(wc_ctx* c, void* out, const void* in, int nrhs, int region, int dagger, hipStream_t st) {
   DiracCanonLaunch a;
@@ -1761,7 +1769,7 @@ int wc_apply_D(wc_ctx* c, void* out, const void* in, int nrhs, int prec, int reg
     require(region == WC_FULL || region == WC_BLOCKS, WC_ERR_ARG, "bad region");
     require(c->have_clover, WC_ERR_STATE, "clover term not created");
     hipStream_t st = S(stream);
-    if (prec == WC_F64) {
+    if (apply_on_canon(c, prec)) {
       apply_D_canon(c, out, in, nrhs, region, dagger, st);
       return;
     }
@@ -1824,7 +1832,7 @@ int wc_apply_D_noalloc(wc_ctx* c, void* out, const void* in, int nrhs, int prec,
             "wc_apply_D_noalloc: " + std::to_string(need >> 20) + " MiB of scratch needed for this lattice, nrhs " +
                 "and precision; the limit is " + std::to_string(SCRATCH_BYTES >> 20) + " MiB");
     hipStream_t st = S(stream);
-    if (prec == WC_F64) {
+    if (apply_on_canon(c, prec)) {
       apply_D_canon(c, out, in, nrhs, region, dagger, st);
       return;
     }
@@ -2178,22 +2186,30 @@ static double time_launches(wc_ctx* c, hipStream_t st, int iters, const std::fun
   return double(ms) / iters;
 }
 
+// mean time of D_w on packed fields (canon false) or on canonical arrays (FP64)
+static double bench_dirac(wc_ctx* c, int prec, int nrhs, int region, int iters, bool canon, hipStream_t st) {
+  Batch& B = ctx_batch(c, nrhs);
+  B.ain[prec].ensure(prec, B.sites_rhs);
+  B.aout[prec].ensure(prec, B.sites_rhs);
+  HIPCK(hipMemsetAsync(B.ain[prec].data(), 0, spinor_bytes(prec, B.sites_rhs), st));
+  if (B.ain[prec].scale()) HIPCK(hipMemsetAsync(B.ain[prec].scale(), 0, sizeof(float) * B.sites_rhs, st));
+  const int nr = pick_nr(c, nrhs, prec, false, 0);
+  const double ms = time_launches(c, st, iters, [&](hipStream_t s) {
+    if (canon)
+      apply_D_canon(c, B.aout[prec].data(), B.ain[prec].data(), nrhs, region, 0, s);
+    else
+      run_dirac(B, prec, nr, B.ain[prec], B.aout[prec], nullptr, nullptr, nullptr, 0, region == WC_BLOCKS, s);
+  });
+  HIPCK(hipGetLastError());
+  return ms;
+}
+
 int wc_bench_dirac(wc_ctx* c, int prec, int nrhs, int region, int iters, double* ms, void* stream) {
   return guarded([&] {
     require(c && ms && nrhs >= 1 && iters >= 1, WC_ERR_ARG, "bad argument");
     check_prec(prec);
     require(c->have_clover, WC_ERR_STATE, "clover term not created");
-    hipStream_t st = S(stream);
-    Batch& B = ctx_batch(c, nrhs);
-    B.ain[prec].ensure(prec, B.sites_rhs);
-    B.aout[prec].ensure(prec, B.sites_rhs);
-    HIPCK(hipMemsetAsync(B.ain[prec].data(), 0, spinor_bytes(prec, B.sites_rhs), st));
-    if (B.ain[prec].scale()) HIPCK(hipMemsetAsync(B.ain[prec].scale(), 0, sizeof(float) * B.sites_rhs, st));
-    const int nr = pick_nr(c, nrhs, prec, false, 0);
-    *ms = time_launches(c, st, iters, [&](hipStream_t s) {
-      run_dirac(B, prec, nr, B.ain[prec], B.aout[prec], nullptr, nullptr, nullptr, 0, region == WC_BLOCKS, s);
-    });
-    HIPCK(hipGetLastError());
+    *ms = bench_dirac(c, prec, nrhs, region, iters, apply_on_canon(c, prec), S(stream));
   });
 }
 
@@ -2231,6 +2247,7 @@ int wc_autotune(wc_ctx* c, int nrhs, int prec, int nr_out[4], void* stream) {
   return guarded([&] {
     require(c && nrhs >= 1, WC_ERR_ARG, "bad argument");
     check_prec(prec);
+    require(c->have_clover, WC_ERR_STATE, "clover term not created");
     const int cands[4] = {1, 2, 3, 4};
     // D tiles: in prec and, for the outer solver, in FP64 and (16-bit prec) in FP32, the D
     // of the recursion over an F32 basis
@@ -2243,15 +2260,14 @@ int wc_autotune(wc_ctx* c, int nrhs, int prec, int nr_out[4], void* stream) {
       for (int nr : cands) {
         if (nr > nrhs) continue;
         c->nr_dirac[dp] = nr;
-        double t = 0;
-        const int rc = wc_bench_dirac(c, dp, nrhs, WC_FULL, 20, &t, stream);
-        require(rc == WC_OK, rc, g_last_error);
+        const double t = bench_dirac(c, dp, nrhs, WC_FULL, 20, false, S(stream));
         if (t < best) {
           best = t;
           nd = nr;
         }
       }
       c->nr_dirac[dp] = nd;
+      if (dp == P_F64) c->f64_tile_set = false;
     }
     // block-solver tiles of both block solvers in prec
     double best_s = 1e30, best_e = 1e30;
