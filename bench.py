@@ -14,7 +14,7 @@ resident on the device.
     method on the same lattice (and against FP64 with the same block solver);
   * the roofline record of the step's dominant kernel (the block solver's half-sweep over
     all 12 right-hand sides), executed flops and algorithmic bytes per launch, bound by
-    arithmetic intensity against the ridge of the FP32 vector peak and 8 TB/s;
+    arithmetic intensity against the ridge of the FP32 peak of its units and 8 TB/s;
   * D_w GB/s and Gflop/s per storage precision on 16^3 x 32, 24^3 x 48 and 32^3 x 64, and
     with the 12 right-hand sides of 24^3 x 48 in one launch;
   * the uneven batch {8^3 x 16, 12^3 x 24, 16^3 x 32} x 4 Gaussian rhs as one solve;
@@ -47,7 +47,9 @@ FP32_PACKED_PEAK_TFLOPS = 157.3
 # FP32 rate of the kernels as built (packed FP32 instructions switched off): 256 CUs x 4
 # SIMDs x 16 lanes x 2 flop per FMA x 2.4 GHz
 FP32_PEAK_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12
-RIDGE_FLOP_PER_B = FP32_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9)
+# FP32 rate of the matrix cores: a 4x4x1 instruction (16 products, 512 flop) takes a SIMD 8 cycles
+FP32_MATRIX_PEAK_TFLOPS = 256 * 4 * (512 / 8) * 2.4e9 / 1e12
+VALU_CYCLES, MFMA_CYCLES = 4, 8  # of a wave64 vector and of a 4x4x1 matrix instruction
 
 DW_FLOPS = 1320 + 504          # nominal flops per site of D_w
 HOP_FLOPS = 144                # project 12 + SU(3) x half spinor 132 per hop
@@ -233,35 +235,55 @@ def measured_valu(kernel, path):
     return _current_record(path, kernel)
 
 
-def valu_record(csv_path, out_json, kernel="k_sap_eo<3, 1, false>", simds=1024, xcds=8):
-    """VALU occupancy of the block solver from a rocprofv3 --pmc SQ_INSTS_VALU GRBM_GUI_ACTIVE
-    run of `bench.py --profile`, whose last timing loops are 20+ launches without MR steps
-    and then 20+ with them: SQ_INSTS_VALU x 4 cycles per wave64 instruction over the SIMDs
-    and the launch's cycles per XCD (GRBM_GUI_ACTIVE / xcds), for the launch with MR steps,
-    the one without (set-up, odd half, stores) and their difference (the MR steps)."""
+def valu_record(csv_path, out_json, kernel=None, simds=1024, xcds=8):
+    """Issue occupancy of the block solver from a rocprofv3 --pmc SQ_INSTS_VALU [SQ_INSTS_MFMA]
+    GRBM_GUI_ACTIVE run of `bench.py --profile`, whose last timing loops are 20+ launches
+    without MR steps and then 20+ with them: the cycles that the vector (4 per wave64
+    instruction) and matrix instructions (8; SQ_INSTS_VALU counts them too) hold a SIMD, over
+    the SIMDs and the launch's cycles per XCD (GRBM_GUI_ACTIVE / xcds), for the launch with MR
+    steps, the one without (set-up, odd half, stores) and their difference (the MR steps).
+    kernel: the last block solver launched, unless named."""
     import csv
-    per = {}
+    by_kernel, last_of = {}, {}
     for r in csv.DictReader(open(csv_path)):
         short = r["Kernel_Name"].replace("void ", "").replace("wc::", "").split("(")[0]
-        if short == kernel:
-            per.setdefault(int(r["Dispatch_Id"]), {})[r["Counter_Name"]] = float(r["Counter_Value"])
+        if not short.startswith("k_sap_"):
+            continue
+        i = int(r["Dispatch_Id"])
+        by_kernel.setdefault(short, {}).setdefault(i, {})[r["Counter_Name"]] = float(r["Counter_Value"])
+        last_of[short] = max(i, last_of.get(short, i))
+    kernel = kernel or max(last_of, key=last_of.get, default=None)
+    if kernel not in by_kernel:
+        raise ValueError(f"no launch of the block solver {kernel or ''} in {csv_path}")
+    per = by_kernel[kernel]
     ids = sorted(per)
     last = per[ids[-1]]["SQ_INSTS_VALU"]
     with_mr = ids[-20:]
     without = [i for i in ids if abs(per[i]["SQ_INSTS_VALU"] - last) > 0.01 * last][-20:]
+    if not without:
+        raise ValueError(f"no launch of {kernel} without MR steps in {csv_path}")
 
     def mean(sel, c):
         return sum(per[i][c] for i in sel) / len(sel)
 
-    def busy(v, g):
-        return v * 4 / (simds * g / xcds)
+    has_mfma = "SQ_INSTS_MFMA" in per[ids[-1]]
+
+    def busy(v, m, g):
+        return ((v - m) * VALU_CYCLES + m * MFMA_CYCLES) / (simds * g / xcds)
 
     v4, g4 = mean(with_mr, "SQ_INSTS_VALU"), mean(with_mr, "GRBM_GUI_ACTIVE")
     v0, g0 = mean(without, "SQ_INSTS_VALU"), mean(without, "GRBM_GUI_ACTIVE")
+    m4, m0 = (mean(s, "SQ_INSTS_MFMA") if has_mfma else 0.0 for s in (with_mr, without))
+    k = {"valu_busy_launch": busy(v4, m4, g4), "valu_busy_without_mr_steps": busy(v0, m0, g0),
+         "valu_busy_mr_steps": busy(v4 - v0, m4 - m0, g4 - g0), "valu_instructions_per_launch": v4}
+    if has_mfma:
+        k.update({"mfma_instructions_per_launch": m4, "valu_instructions_mr_steps": v4 - m4 - (v0 - m0),
+                  "mfma_instructions_mr_steps": m4 - m0,
+                  "mfma_share_of_busy_launch": m4 * MFMA_CYCLES / ((v4 - m4) * VALU_CYCLES + m4 * MFMA_CYCLES)})
     rec = {"csrc_sha256": csrc_sha256(),
-           "command": "rocprofv3 --pmc SQ_INSTS_VALU ... GRBM_GUI_ACTIVE --output-format csv -- python bench.py --profile",
-           "kernels": {kernel: {"valu_busy_launch": busy(v4, g4), "valu_busy_without_mr_steps": busy(v0, g0),
-                                "valu_busy_mr_steps": busy(v4 - v0, g4 - g0), "valu_instructions_per_launch": v4}}}
+           "command": "rocprofv3 --pmc SQ_INSTS_VALU SQ_INSTS_MFMA ... GRBM_GUI_ACTIVE --output-format csv -- "
+                      "python bench.py --profile",
+           "kernels": {kernel: k}}
     json.dump(rec, open(out_json, "w"), indent=1)
     return rec
 
@@ -374,10 +396,26 @@ def tune_c4(wc, torch, lat, pts):
             "basis_trial_ms": basis_ms, "tuning_s": time.perf_counter() - t0}
 
 
-def roofline_record(lat, V, prec, nrhs, block, label, tile=1):
+MM_TILE = 4  # rhs per work-group of the matrix-core block solver
+
+
+def block_solver(wc, lat, nrhs, prec):
+    """(kernel, tile) of the even/odd block solver in a call with nrhs right-hand sides: which
+    kernel the library takes, as it asks for it, and the rhs that a work-group shares the block
+    operator across (the matrix-core kernel takes tiles as equal as possible)."""
+    tile = wc.sap_eo_tiles([lat], [nrhs], prec)[0]
+    code = {"f64": 0, "f32": 1, "f16": 2, "bf16": 3}[prec]
+    if tile == MM_TILE:
+        groups = -(-nrhs // MM_TILE)
+        return f"k_sap_eo_mm<{code}>", -(-nrhs // groups)
+    return f"k_sap_eo<{code}, {tile}, false>", tile
+
+
+def roofline_record(lat, V, prec, nrhs, block, label, tile=1, peak=FP32_PEAK_TFLOPS):
     """Roofline of the block solver's half-sweep (one colour, NMR steps, even/odd) timed
     inside the library with HIP events on its launch stream; the block operator counts once
-    per tile of `tile` right-hand sides (the rhs a work-group shares it across)."""
+    per tile of `tile` right-hand sides (the rhs a work-group shares it across), and `peak` is
+    the FP32 rate of the units that its products run on, in TFLOP/s."""
     ms0 = lat.bench_sap(prec=prec, nrhs=nrhs, nmr=0, eo=True, iters=20)
     ms = lat.bench_sap(prec=prec, nrhs=nrhs, nmr=NMR, eo=True, iters=20)
     sites = V // 2 * nrhs
@@ -386,15 +424,16 @@ def roofline_record(lat, V, prec, nrhs, block, label, tile=1):
     byts = half_sweep_bytes(prec, tile) * sites
     tf = flops / (ms * 1e-3) / 1e12
     ai = flops / byts
-    bound = "alu" if ai > RIDGE_FLOP_PER_B else "hbm"
+    ridge = peak * 1e12 / (HBM_PEAK_GBS * 1e9)
+    bound = "alu" if ai > ridge else "hbm"
     rec = {"bound": bound, "kernel": label, "launch_ms": ms,
            "alg_flops_per_launch": flops, "alg_bytes_per_launch": byts,
-           "nominal_flops_per_launch": nominal, "arith_intensity": ai, "ridge": RIDGE_FLOP_PER_B,
-           "TFLOPs_executed": tf, "frac_of_fp32_peak": tf / FP32_PEAK_TFLOPS,
+           "nominal_flops_per_launch": nominal, "arith_intensity": ai, "ridge": ridge, "rhs_per_work_group": tile,
+           "TFLOPs_executed": tf, "fp32_peak": peak, "frac_of_fp32_peak": tf / peak,
            "frac_of_packed_fp32_peak": tf / FP32_PACKED_PEAK_TFLOPS,
            "GBps_alg": byts / (ms * 1e-3) / 1e9, "frac_hbm": byts / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS}
     if bound == "alu":
-        rec.update({"achieved": tf, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": tf / FP32_PEAK_TFLOPS})
+        rec.update({"achieved": tf, "peak": peak, "unit": "TFLOP/s", "frac": tf / peak})
     else:
         g = rec["GBps_alg"]
         rec.update({"achieved": g, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": g / HBM_PEAK_GBS})
@@ -654,7 +693,8 @@ def profile_run(wc, torch, dev):
     p = params(wc, storage, True, basis_prec=basis)
     lat.solve(pts, p)
     (_, st), ms = sync_time(torch, lambda: lat.solve(pts, p))
-    rf = roofline_record(lat, 663552, storage, 12, BLOCK, f"even/odd block solver on {storage} storage, 24^3x48 x 12 rhs")
+    kernel, tile = block_solver(wc, lat, 12, storage)
+    rf = roofline_record(lat, 663552, storage, 12, BLOCK, f"{kernel}, 24^3x48 x 12 rhs", tile=tile)
     dw = dirac_rates(lat, 663552, ("f64", storage), nrhs=12, iters=20)
     print(json.dumps({"profile": "24^3x48 x 12 point sources", "storage": storage, "basis": basis, "solve_ms": ms,
                       "iters": max(s["iters"] for s in st), "half_sweep_ms": rf["launch_ms"],
@@ -740,8 +780,8 @@ def main():
         summarise_pmc(sys.argv[2], sys.argv[3], sys.argv[4])
         return
     if len(sys.argv) > 1 and sys.argv[1] == "--valu-record":
-        # --valu-record CSV OUT_JSON
-        valu_record(sys.argv[2], sys.argv[3])
+        # --valu-record CSV OUT_JSON [KERNEL]
+        valu_record(sys.argv[2], sys.argv[3], *sys.argv[4:5])
         return
     if len(sys.argv) > 1 and sys.argv[1] == "--counter-summary":
         # --counter-summary CSV OUT_MD COMMAND [MATCH]
@@ -817,14 +857,14 @@ def main():
     del r
     value = 12 / (ms_per_step * 1e-3)
     flops = sum(solve_flops(V, s["iters"], s["restarts"], NKV, NCY, NMR, block, True) for s in st)
-    etile = tuning["tiles"][storage][3]
+    kernel, tile = block_solver(wc, lat, 12, storage)
+    matrix = kernel.startswith("k_sap_eo_mm")
     roofline = roofline_record(lat, V, storage, 12, block,
-                               f"even/odd block solver on {storage} storage (k_sap_eo_mm on the matrix cores "
-                               f"where the library picks it, else k_sap_eo): one colour of 24^3x48 x 12 rhs, "
-                               f"{NMR} steps", tile=etile)
-    pcode = {"f32": 1, "f16": 2, "bf16": 3}[storage]
-    roofline["traffic"] = measured_traffic(f"k_sap_eo<{pcode}, {etile}, false>", "traffic_24c48.json")
-    roofline["valu_occupancy"] = measured_valu(f"k_sap_eo<{pcode}, {etile}, false>", "valu_24c48.json")
+                               f"{kernel}: even/odd block solver on the {'matrix' if matrix else 'vector'} units, "
+                               f"{tile} rhs per work-group, one colour of 24^3x48 x 12 rhs, {NMR} steps", tile=tile,
+                               peak=FP32_MATRIX_PEAK_TFLOPS if matrix else FP32_PEAK_TFLOPS)
+    roofline["traffic"] = measured_traffic(kernel, "traffic_24c48.json")
+    roofline["valu_occupancy"] = measured_valu(kernel, "valu_24c48.json")
 
     extras = {}
     if not args.no_extras:
