@@ -83,7 +83,8 @@ static hipGraphExec_t capture_graph(hipStream_t cap, const std::function<void(hi
 // Device memory of destroyed contexts and finished calls, kept for the next ones: a program
 // that builds a context per gauge field (a molecular-dynamics step, a differentiated
 // application) otherwise spends longer in hipMalloc and hipFree than in its kernels (12^3 x 24
-// dirac_apply and its gradients: 1.39 ms a call with them, 0.45 ms of kernels).  A block enters
+// dirac_apply and its gradients: 1.39 ms a call with them, 0.62 without; 0.43 with the link
+// derivative's present kernels, of which 0.25 ms are kernels).  A block enters
 // the pool only when no work on any stream can still use it (its giver has waited for that),
 // so whoever takes it next, on any stream or thread, may write it at once.  At most POOL_BYTES
 // per device are kept; the blocks kept longest go back to the runtime for new ones, all of a

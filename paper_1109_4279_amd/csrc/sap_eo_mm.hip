@@ -16,12 +16,14 @@
 //
 // What bounds it: issue.  k_sap_eo issues 1957 vector instructions per wavefront of 64
 // (site, rhs) and MR step, two thirds of them the FMAs of these products and the decoding of
-// the operator per rhs; here a wavefront issues 1276 vector and 576 matrix instructions for 128
-// of them.  A 4x4x1 matrix instruction holds its SIMD for 8 cycles, and vector instructions do
-// not run beside it; with two wavefronts per SIMD the MR steps take 22 000 cycles against
-// 19 400 of issue.  24^3 x 48, 12 rhs, BF16: half-sweep 1460 (k_sap_eo) -> 1067 us, of it
-// set-up and stores 507 us, an MR step 140 us (214 us).  (With the matrix instructions in runs
-// of 24 instead of 48, see mm_hops, and the field addresses spilled over the MR loop: 1213 us.)
+// the operator per rhs; here a wavefront issues 1257 vector and 576 matrix instructions for 128
+// of them (SQ_INSTS_VALU, which counts both, and SQ_INSTS_MFMA, launches of 4 steps less launches
+// of none).  A 4x4x1 matrix instruction holds its SIMD for 8 cycles (SQ_VALU_MFMA_BUSY_CYCLES),
+// a vector one for 4, and vector instructions do not run beside it: with two wavefronts per SIMD a
+// step of a block takes 22 100 cycles against 19 300 of issue (87 %; set-up and stores 33 %).
+// 24^3 x 48, 12 rhs, BF16: half-sweep 1460 (k_sap_eo) -> 1067 us, of it set-up and stores
+// 507 us, an MR step 140 us (214 us).  (With the matrix instructions in runs of 24 instead of
+// 48, see mm_hops, and the field addresses spilled over the MR loop: 1213 us.)
 //
 // Operator: the block's links are staged in LDS once (9 packed words each); the lane's rows
 // of the two clover blocks of its two sites are kept packed in registers (48 words).  The
