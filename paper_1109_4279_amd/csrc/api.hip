@@ -15,6 +15,7 @@
 #include "wc.h"
 #include "block_pool.h"
 #include "dense_host.h"
+#include "sap_rule.h"
 #include "wc_kernels.h"
 
 namespace wc {
@@ -730,35 +731,13 @@ static int border_entries_of(const std::vector<wc_ctx*>& lat, int bv) {
   return n;
 }
 
-// The rhs tile of the block solver on the blocks of volume bv of a call on lat with nrhs: nr, or, where the choice is
-// left (SAP_MM_RHS), the matrix-core kernel or one rhs per work-group of the vector one.
-//
-// One work item of the matrix-core kernel takes the same time for one to four rhs, so tiles that
-// are not full count as full ones, and it runs in whole rounds: eight wavefronts fit the registers
-// of a CU and as many work-groups as fit its LDS.  The vector kernel keeps its operator in
-// registers up to two items per CU; above that at most four work-groups share a CU, fewer where
-// their LDS does not fit four times.  Measured half-sweeps (us, vector / matrix cores, BF16):
-//   4^4, two per CU      256 blocks 69.5 / 61.9 (2 rhs), 85 / 68 (3), 96 / 70 (4); two rounds
-//                        124 / 125 (5 rhs), 138 / 125 (6), 182 / 133 (8); 1296 blocks 415 / 402
-//                        (3 rhs), 511 / 410 (4), 1461 / 1070 (12)
-//   2x4^3, three per CU  256 blocks 47.0 / 47.4 (3 rhs), 79.9 / 49.0 (4); 648 88.9 / 97.5 (2),
-//                        155 / 101 (3); 1152 170 / 150 (2)
-//   4x3^3, four per CU   256 blocks 50.7 / 48.3 (4 rhs), 79.1 / 62.4 (5); 648 92.9 / 98.4 (2),
-//                        94.7 / 100.6 (3), 135 / 106 (4), 159 / 173 (5); 1152 123 / 150 (2),
-//                        179 / 155 (3), 280 / 265 (5)
-//   4x4x2x2, four per CU 648 blocks 78 / 60 (2 rhs); 1152 114 / 109 (2), 152 / 116 (3), 224 / 178
-//                        (5); 1152 items of one rhs each would be 73 / 112
-//   2^4, four per CU     256 blocks 38.0 / 35.5 (3 rhs), 71 / 38 (6); 2048 140 / 57 (2)
-// that is, a round costs as much as 2.7 items per CU of a vector kernel that runs at most three
-// per CU, and of one that runs four as 4 (one round) or 4.5 and half an item less in all.  In 629
-// combinations of 15 block shapes, 32 to 8192 blocks and 2 to 12 rhs the pick is at most 1 %
-// behind the vector kernel.
+// The rhs tile of the block solver on the blocks of volume bv of a call on lat with nrhs: nr, or,
+// where the choice is left (SAP_MM_RHS), the matrix-core kernel or one rhs per work-group of the
+// vector one, whichever sap_rule.h finds the faster.
 static int sap_tile(const std::vector<wc_ctx*>& lat, const std::vector<int>& nrhs, int nr, int bv) {
   if (nr != SAP_MM_RHS) return nr;
   if (lat[0]->opt_sap_cache >= 0) return 1;  // (asked for the vector kernel, one way or the other)
   const int entries = border_entries_of(lat, bv);
-  const size_t mm_lds = sap_eo_mm_lds_bytes(bv, entries);
-  if (mm_lds > LDS_MAX_BYTES) return 1;
   long long vec = 0, mat = 0;
   for (size_t i = 0; i < lat.size(); ++i) {
     if (lat[i]->g.bvol != bv) continue;
@@ -766,12 +745,9 @@ static int sap_tile(const std::vector<wc_ctx*>& lat, const std::vector<int>& nrh
     vec += blocks * nrhs[i];
     mat += blocks * ((nrhs[i] + SAP_MM_RHS - 1) / SAP_MM_RHS);
   }
-  const long long cus = device_cus();
-  const long long at_once = cus * std::min<long long>(SAP_MM_CU_WAVES / sap_eo_mm_waves(bv), LDS_MAX_BYTES / mm_lds);
-  const double rounds = double((mat + at_once - 1) / at_once);
-  const bool four_per_cu = 4 * sap_eo_lds_bytes(P_BF16, 1, bv, entries) <= LDS_MAX_BYTES;
-  const double vec_per_cu = four_per_cu ? 4.5 * rounds - 0.5 : 2.7 * rounds;
-  return vec_per_cu * cus < vec ? SAP_MM_RHS : 1;
+  const bool faster = sap_mm_faster(vec, sap_eo_waves(bv), sap_eo_lds_bytes(P_BF16, 1, bv, entries), mat,
+                                    sap_eo_mm_waves(bv), sap_eo_mm_lds_bytes(bv, entries), LDS_MAX_BYTES, device_cus());
+  return faster ? SAP_MM_RHS : 1;
 }
 
 // odd_rho: residual on odd sites for the even/odd solver (see SapLaunch::odd_rho)
@@ -822,7 +798,7 @@ static void run_sap_halfsweep(Batch& B, int prec, int nr, int colour, int nmr, F
     if (mm)
       launch_sap_eo_mm(prec, a, bv, bentries, st);
     else if (eo)
-      launch_sap_eo(prec, tile, a, persistent_grid(it.n, 4), bv, st);
+      launch_sap_eo(prec, tile, a, persistent_grid(it.n, SAP_EO_PER_CU), bv, st);
     else if (is16(prec) && tile == 2 && bv == 256)
       launch_sap_mr_lds(prec, tile, a, persistent_grid(it.n, 1), st);
     else

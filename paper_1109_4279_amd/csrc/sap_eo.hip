@@ -580,7 +580,7 @@ __global__ __launch_bounds__(64 * EO_MAX_WAVES) void k_sap_eo(SapLaunch a) {
   }
 }
 
-static int eo_threads(int max_bvol) { return (2 * ((max_bvol + 1) / 2) + 63) / 64 * 64; }
+int sap_eo_waves(int max_bvol) { return (2 * ((max_bvol + 1) / 2) + 63) / 64; }
 
 size_t sap_eo_lds_bytes(int prec, int nr, int max_bvol, int border_entries) {
   const size_t cb = prec == P_F64 ? 16 : 8;
@@ -605,7 +605,7 @@ static void launch_p(const SapLaunch& a, int nr, int grid, int threads, size_t l
 
 void launch_sap_eo(int prec, int nr, const SapLaunch& a, int grid, int max_bvol, hipStream_t st) {
   const size_t lds = sap_eo_lds_bytes(prec, nr, max_bvol, a.border_entries);
-  const int threads = eo_threads(max_bvol);
+  const int threads = 64 * sap_eo_waves(max_bvol);
   switch (prec) {
     case P_F64: launch_p<P_F64>(a, nr, grid, threads, lds, st); break;
     case P_F32: launch_p<P_F32>(a, nr, grid, threads, lds, st); break;

@@ -89,13 +89,13 @@ void launch_sap_eo(int prec, int nr, const SapLaunch& a, int grid, int max_bvol,
 // dynamic LDS of the even/odd solver: reduction scratch, the exchange rows and, when
 // border_entries > 0, the border update's entries
 size_t sap_eo_lds_bytes(int prec, int nr, int max_bvol, int border_entries);
+int sap_eo_waves(int max_bvol);  // wavefronts of its work-group
 // the same solver for several rhs per work-group (up to SAP_MM_RHS) on the matrix cores,
 // 16-bit storage: LDS bytes of its exchange slots (or border entries) and in all
 constexpr int SAP_MM_RHS = 4;
 size_t sap_eo_mm_xch_bytes(int bvol, int border_entries);
 size_t sap_eo_mm_lds_bytes(int bvol, int border_entries);
-constexpr int SAP_MM_CU_WAVES = 8;  // its wavefronts on a CU (256 registers each)
-int sap_eo_mm_waves(int bvol);      // and in a work-group
+int sap_eo_mm_waves(int bvol);  // wavefronts of its work-group
 // its clover operand from the 16-bit even/odd clover field: SAP_MM_CLOVER_BYTES per site
 constexpr size_t SAP_MM_CLOVER_BYTES = 8 * 9 * 4;
 void launch_clover_mm(int V, const void* clov_eo16, void* dst, hipStream_t st);
